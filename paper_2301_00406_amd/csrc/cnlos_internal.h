@@ -409,8 +409,8 @@ struct NcGeo {
   int n, m;
   double wall, range, cdt, ix, iy;
   int literal;
+  int plain;      // set by the launchers: distances beyond the fast path's range
 };
-size_t nc_forward_lds_bytes(int m);
 hipError_t launch_nc_forward(const NcGeo& g, const float* u, float* tau, hipStream_t st);
 hipError_t launch_nc_transpose(const NcGeo& g, const float* tau, float* u, hipStream_t st);
 

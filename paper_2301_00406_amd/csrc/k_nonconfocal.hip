@@ -14,21 +14,27 @@
 // R = m c dt / 2, and time bin b holding path lengths in [b, b + 1) c dt.
 //
 // The time bin is an integer that floating point decides, so it is computed
-// in FP64 with every operation in the order written here and no contraction
-// into fused multiply-adds; the weight and the sums are FP64 as well, and only
-// the stored results are FP32.  Both kernels are deterministic: the forward
-// sums each detector's bins in a fixed order (a wave's lanes take consecutive
-// depths of one column, whose bins never decrease with depth, and a segmented
-// scan over equal bins leaves one writer per bin; each wave owns a histogram),
-// and the transpose gathers over the detectors in index order.
+// in FP64 and decided as the operations written here in order (no contraction
+// into fused multiply-adds) decide it; the weight and the sums are FP64 as
+// well, and only the stored results are FP32.  Both kernels are deterministic:
+// every histogram bin and every voxel is summed in a fixed order.
+//
+// What bounds them: FP64 vector instructions.  Written plainly, a path costs
+// two correctly rounded square roots and two correctly rounded divisions (each
+// a dozen dependent FP64 instructions).  Here it costs one reciprocal square
+// root r of d_d^2 (v_rsq_f64 and one third-order step: full FP64 accuracy),
+// since d_d = d_d^2 r and 1 / d_d^2 = r^2, and a product with 1 / (c dt) instead
+// of the bin's division.  That product can fall on the other side of a whole
+// number only when it is within a few rounding errors of one: such paths
+// (kNearBin; about one in 10^7) take the plain form, so every bin is the one
+// that the plain form gives.
 #include "cnlos_internal.h"
 
 namespace cnlos {
 
 namespace {
 
-constexpr int kNcWaves = 4;          // waves per block of the forward kernel
-constexpr int kNcThreads = 64 * kNcWaves;
+constexpr int kNcMaxWaves = 8;       // waves per block of the forward kernel
 constexpr int kNcMaxGridDev = 256;   // detectors per side (the host checks it)
 
 struct NcPath {
@@ -66,106 +72,358 @@ __device__ __forceinline__ double nc_illum_dist(const NcGeo& g, double xv, doubl
   return sqrt((ex * ex + ey * ey) + z * z);
 }
 
-// Lateral positions of the n columns and depths of the m bins, once per block
-// (FP64, the same operations as nc_lateral / nc_depth).
-__device__ __forceinline__ void nc_positions(const NcGeo& g, double* xs, double* zs, int nt) {
-  for (int i = threadIdx.x; i < g.n; i += nt) xs[i] = nc_lateral(g, i);
-  if (zs)
-    for (int k = threadIdx.x; k < g.m; k += nt) zs[k] = nc_depth(g, k);
-  __syncthreads();
+// 1 / sqrt(x) to FP64 accuracy for x in [1e-120, 1e120] (NcGeo::plain is set
+// when a geometry could leave that range): v_rsq_f64 is good to about 2^-24,
+// the third-order step leaves an error of order 2^-70 before rounding
+__device__ __forceinline__ double nc_rsqrt(double x) {
+  const double r = __builtin_amdgcn_rsq(x);
+  const double h = fma(-(x * r), r, 1.0);
+  return fma(r * h, fma(0.375, h, 0.5), r);
 }
 
-// tau[det][b] = sum over voxels with path bin b of w u.  One block per
-// detector; wave w takes the (column, 64-depth chunk) items w, w + 4, ... in
-// order, lane l the depth 64 c + l of the chunk.
-__global__ void __launch_bounds__(kNcThreads)
+// z for the body of a rarely taken branch.  The compiler counts a square root
+// or a division as one operation: it would compute the body for every path,
+// or lift a root out of two such bodies (30.9 and 14.8 ms at 64x64x512 with
+// one and two detectors per block); a value that it cannot see through keeps
+// them where they are.
+__device__ __forceinline__ double nc_in_branch(double z) {
+  asm volatile("" : "+v"(z));
+  return z;
+}
+
+// distance to a whole number below which the bin is decided by nc_path: the
+// error of the fast quotient is below 8 roundings of at most 1024
+constexpr double kNearBin = 1e-8;
+
+// A path from its squared detector distance d2 = (ex^2 + ey^2) + z^2 and the
+// voxel's illumination distance di: the bin, and 1 / d_d^2.
+struct NcFast {
+  int bin;
+  bool near;    // decide the bin with nc_path
+  double r2;
+};
+__device__ __forceinline__ NcFast nc_fast(double d2, double di, double inv_cdt, int m) {
+  const double r = nc_rsqrt(d2);
+  const double q = fma(d2, r, di) * inv_cdt;
+  // the nearest whole number through the addition of 1.5 2^52 (q < 2^30, see
+  // nc_in_range): its low word is the integer
+  const double t = q + 6755399441055744.0;
+  const double off = q - (t - 6755399441055744.0);      // [-1/2, 1/2], exact
+  NcFast f;
+  f.bin = min(__double2loint(t) + (__double2hiint(off) >> 31), m);
+  f.near = fabs(off) < kNearBin;
+  f.r2 = r * r;
+  return f;
+}
+
+// sum into one bin of a histogram that only this wave writes; the callers
+// never let two lanes of an instruction name the same bin, so the order of a
+// bin's terms is the program's (no return value: the wave does not wait)
+__device__ __forceinline__ void nc_bin_add(double* h, double v) {
+  (void)__hip_atomic_fetch_add(h, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// Place of bin b in a histogram.  Lanes are S depths apart, so their bins are up
+// to S apart: a pad every 8 bins keeps such strides off shared banks.
+__host__ __device__ constexpr int nc_place(int b) { return b + (b >> 3); }
+constexpr int kNcRow = 72;   // LDS row of u by [j][lane] (the pad spreads the transposed stores)
+
+// tau[det][b] = sum over voxels with path bin b of w u.  One block per D
+// detectors; wave w takes the columns w, w + W, ... in order, and lane l
+// the S = ceil(m / 64) consecutive depths from S l on, so that
+//   - the illumination distance and u of a voxel serve D detectors;
+//   - a lane's bins never decrease from one depth to the next (the path grows
+//     with the depth): a lane sums a run of equal bins in a register and adds
+//     it to its wave's histogram when the bin changes;
+//   - two lanes never add to one bin in the same step: if lane l's run ends at
+//     step j, a lane above it whose bin is the same has not reached a new bin
+//     either, since all its depths are larger.  Only the runs left at the end
+//     of a column can meet; they are added in lane order.
+// A column's u is read coalesced (SM >= S loads, the next column's while this
+// one is summed) and handed to the lanes through LDS: read in place, at a
+// stride of S floats, the columns of a CU's waves overrun its L1 (64x64x512,
+// one detector per block: 15.0 against 13.8 ms).
+// Consecutive depths in consecutive lanes, with a segmented scan over equal
+// bins per 64 paths (18 lane exchanges through the LDS pipe), and the plain path
+// arithmetic took 42.6 ms at 64x64x512 and 1.59 ms at 32x32x256; now 11.8 and
+// 0.44 ms, issuing vector instructions in about three quarters of the cycles.
+template <int D, bool LIT, int SM>
+__global__ void __launch_bounds__(64 * kNcMaxWaves)
 k_nc_forward(NcGeo g, const float* __restrict__ u, float* __restrict__ tau) {
-  extern __shared__ double nc_lds[];           // histograms [kNcWaves][m], then depths [m]
+  // histograms [W][D][M], z [S][64] by [j][lane], then u [W][S][kNcRow]
+  extern __shared__ double nc_lds[];
   __shared__ double xs[kNcMaxGridDev];
-  const int m = g.m, n = g.n;
-  double* zs = nc_lds + kNcWaves * m;
-  const int det = blockIdx.x, i = det / n, j = det - i * n;
+  const int m = g.m, n = g.n, S = (m + 63) >> 6, nt = blockDim.x, W = nt >> 6;
+  const int M = nc_place(m);                   // places of one histogram
+  double* zs = nc_lds + W * D * M;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  for (int b = threadIdx.x; b < kNcWaves * m; b += kNcThreads) nc_lds[b] = 0.0;
-  nc_positions(g, xs, zs, kNcThreads);
-  const double xd = xs[i], yd = xs[j];
-  const int nchunk = (m + 63) >> 6;
-  const int items = n * n * nchunk;
-  double* h = nc_lds + wv * m;
-  for (int it = wv; it < items; it += kNcWaves) {
-    const int col = it / nchunk, k = (it - col * nchunk) * 64 + lane;
-    const int p = col / n, q = col - p * n;
-    double val = 0.0;
-    int bin = m;
-    if (k < m) {
-      const double xv = xs[p], yv = xs[q], z = zs[k];
-      const NcPath r = nc_path(g, xd, yd, xv, yv, z, nc_illum_dist(g, xv, yv, z));
-      bin = r.bin;
-      val = r.bin < m ? r.w * (double)u[(size_t)col * m + k] : 0.0;
-    }
-    // segmented inclusive scan over runs of equal bins (bins never decrease
-    // with the lane: the path grows with the depth)
+  for (int b = threadIdx.x; b < W * D * M; b += nt) nc_lds[b] = 0.0;
+  for (int i = threadIdx.x; i < n; i += nt) xs[i] = nc_lateral(g, i);
+  for (int i = threadIdx.x; i < 64 * S; i += nt) zs[i] = nc_depth(g, S * (i & 63) + (i >> 6));
+  __syncthreads();
+  // this lane's depths 64 i + lane in the order they are read from memory, and
+  // their places by [j][lane]: k = S l + j (k S' >> 16 = k / S for k < 1024)
+  float* ub = reinterpret_cast<float*>(zs + 64 * S) + wv * S * kNcRow;
+  const int inv_s = (65536 + S - 1) / S;
+  int place[SM];
 #pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const double v2 = __shfl_up(val, d, 64);
-      const int b2 = __shfl_up(bin, d, 64);
-      val += (lane >= d && b2 == bin) ? v2 : 0.0;
+  for (int i = 0; i < SM; ++i) {
+    const int k = min(64 * i + lane, 64 * S - 1), l = (k * inv_s) >> 16;
+    place[i] = (k - l * S) * kNcRow + l;
+  }
+  float nu[SM];
+  auto load_column = [&](int col) {
+    const float* uc = u + (size_t)col * m;
+#pragma unroll
+    for (int i = 0; i < SM; ++i) nu[i] = uc[min(64 * i + lane, m - 1)];
+  };
+  if (wv < n * n) load_column(wv);
+  double xd[D], yd[D];
+#pragma unroll
+  for (int d = 0; d < D; ++d) {
+    const int det = min((int)blockIdx.x * D + d, n * n - 1);
+    xd[d] = xs[det / n];
+    yd[d] = xs[det % n];
+  }
+  const double inv_cdt = 1.0 / g.cdt;
+  double* h = nc_lds + wv * D * M;
+  for (int col = wv; col < n * n; col += W) {
+    const double xv = xs[col / n], yv = xs[col % n];
+    double lat_i, lat_d[D];
+    {
+#pragma clang fp contract(off)
+      const double ex = xv - g.ix, ey = yv - g.iy;
+      lat_i = ex * ex + ey * ey;
+#pragma unroll
+      for (int d = 0; d < D; ++d) {
+        const double fx = xv - xd[d], fy = yv - yd[d];
+        lat_d[d] = fx * fx + fy * fy;
+      }
     }
-    const int bn = __shfl_down(bin, 1, 64);
-    if ((lane == 63 || bn != bin) && bin < m) h[bin] += val;
+    // only this wave's lanes touch ub, and a wave's LDS accesses are in order
+#pragma unroll
+    for (int i = 0; i < SM; ++i)
+      if (i < S) ub[place[i]] = nu[i];
+    if (col + W < n * n) load_column(col + W);
+    __builtin_amdgcn_wave_barrier();
+    int cur[D];
+    double acc[D];
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+      cur[d] = m;
+      acc[d] = 0.0;
+    }
+    double z = zs[lane];
+    float uf = ub[lane];
+    for (int j = 0; j < S; ++j) {
+      const int k = S * lane + j;
+      const bool in = k < m;
+      // the next step's operands are read before this one's arithmetic
+      const int jn = min(j + 1, S - 1);
+      const double zn = zs[64 * jn + lane];
+      const float un = ub[jn * kNcRow + lane];
+      const double uv = (double)uf;
+      double zz, d2i;
+      {
+#pragma clang fp contract(off)
+        zz = z * z;
+        d2i = lat_i + zz;
+      }
+      const double ri = nc_rsqrt(d2i);
+      const double di = d2i * ri;
+      const double wu = LIT ? uv * (ri * ri) : uv;
+      NcFast f[D];
+      double val[D];
+      bool near = g.plain != 0;
+#pragma unroll
+      for (int d = 0; d < D; ++d) {
+        f[d] = nc_fast(lat_d[d] + zz, di, inv_cdt, m);
+        near |= f[d].near;
+        val[d] = LIT ? wu * f[d].r2 : wu;
+      }
+      if (near) {
+        const double zp = nc_in_branch(z);
+        const double dp = nc_illum_dist(g, xv, yv, zp);
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+          const NcPath r = nc_path(g, xd[d], yd[d], xv, yv, zp, dp);
+          f[d].bin = r.bin;
+          if (g.plain) val[d] = r.w * uv;
+        }
+      }
+#pragma unroll
+      for (int d = 0; d < D; ++d) {
+        const int bin = in ? f[d].bin : m;
+        if (bin != cur[d]) {
+          if (cur[d] < m) nc_bin_add(h + d * M + nc_place(cur[d]), acc[d]);
+          cur[d] = bin;
+          acc[d] = 0.0;
+        }
+        acc[d] += val[d];
+      }
+      z = zn;
+      uf = un;
+    }
+    __builtin_amdgcn_wave_barrier();
+    // the runs left: lanes whose run continues their predecessor's add after it
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+      const int prev = __shfl_up(cur[d], 1, 64);
+      unsigned long long same = __ballot(lane > 0 && prev == cur[d] && cur[d] < m);
+      unsigned long long todo = __ballot(cur[d] < m);
+      while (todo) {                             // at most 64 rounds: `same` loses a lane each
+        const unsigned long long now = todo & ~same;
+        if ((now >> lane) & 1) nc_bin_add(h + d * M + nc_place(cur[d]), acc[d]);
+        todo &= same;
+        same &= same << 1;
+      }
+    }
   }
   __syncthreads();
-  for (int b = threadIdx.x; b < m; b += kNcThreads) {
-    double s = 0.0;
 #pragma unroll
-    for (int w = 0; w < kNcWaves; ++w) s += nc_lds[w * m + b];
-    tau[(size_t)det * m + b] = (float)s;
+  for (int d = 0; d < D; ++d) {
+    const int det = blockIdx.x * D + d;
+    if (det >= n * n) break;
+    for (int b = threadIdx.x; b < m; b += nt) {
+      double s = 0.0;
+      for (int w = 0; w < W; ++w) s += nc_lds[(w * D + d) * M + nc_place(b)];
+      tau[(size_t)det * m + b] = (float)s;
+    }
   }
 }
 
-// u[p][q][k] = sum over detectors (in index order) of w tau[det][bin].
-__global__ void __launch_bounds__(256)
+// u[p][q][k] = sum over detectors (in index order) of w tau[det][bin].  A wave
+// takes 64 depths of one column, so the squared lateral distances to the
+// detector rows and columns are tables in LDS that the wave reads as
+// broadcasts, and a path's squared distance is two additions (2.61 -> 1.24 ms
+// at 45x45x300, bound by FP64 issue).
+constexpr int kNcTWaves = 4;
+template <bool LIT>
+__global__ void __launch_bounds__(64 * kNcTWaves)
 k_nc_transpose(NcGeo g, const float* __restrict__ tau, float* __restrict__ u) {
-  __shared__ double xs[kNcMaxGridDev];
+  extern __shared__ double nc_lds[];            // [kNcTWaves][2][n]: squared offsets in x, in y
   const int m = g.m, n = g.n;
-  nc_positions(g, xs, nullptr, 256);
-  const size_t V = (size_t)n * n * m;
-  const size_t vox = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (vox >= V) return;
-  const int col = (int)(vox / m), k = (int)(vox - (size_t)col * m);
-  const int p = col / n, q = col - p * n;
-  const double xv = xs[p], yv = xs[q], z = nc_depth(g, k);
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int nchunk = (m + 63) >> 6, items = n * n * nchunk;
+  const int item = min((int)blockIdx.x * kNcTWaves + wv, items - 1);
+  const int col = item / nchunk, k0 = (item - col * nchunk) * 64;
+  const double xv = nc_lateral(g, col / n), yv = nc_lateral(g, col % n);
+  double* lx = nc_lds + wv * 2 * n;
+  double* ly = lx + n;
+  for (int i = lane; i < n; i += 64) {
+#pragma clang fp contract(off)
+    const double ex = xv - nc_lateral(g, i), ey = yv - nc_lateral(g, i);
+    lx[i] = ex * ex;
+    ly[i] = ey * ey;
+  }
+  __syncthreads();
+  const int k = min(k0 + lane, m - 1);
+  const double z = nc_depth(g, k);
   const double di = nc_illum_dist(g, xv, yv, z);
+  double zz;
+  {
+#pragma clang fp contract(off)
+    zz = z * z;
+  }
+  const double inv_cdt = 1.0 / g.cdt;
   double acc = 0.0;
   for (int i = 0; i < n; ++i) {
-    const double xd = xs[i];
-    // loads are unconditional (bin clamped into the column, term masked), so
-    // the unrolled iterations' loads issue together
-#pragma unroll 4
-    for (int j = 0; j < n; ++j) {
-      const NcPath r = nc_path(g, xd, xs[j], xv, yv, z, di);
-      const int b = r.bin < m ? r.bin : m - 1;
-      const float t = tau[(size_t)(i * n + j) * m + b];
-      acc += r.bin < m ? r.w * (double)t : 0.0;
+    const double x2 = lx[i];
+    // four detectors at a time: their loads are unconditional (bin clamped into
+    // the column, term masked) and issue together, and one branch serves the
+    // rare bins of all four
+    for (int j0 = 0; j0 < n; j0 += 4) {
+      NcFast f[4];
+      double w[4];
+      bool near = g.plain != 0;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        f[q] = nc_fast((x2 + ly[min(j0 + q, n - 1)]) + zz, di, inv_cdt, m);
+        near |= f[q].near;
+        w[q] = LIT ? f[q].r2 : 1.0;
+      }
+      if (near) {
+        const double zp = nc_in_branch(z);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const NcPath r = nc_path(g, nc_lateral(g, i), nc_lateral(g, min(j0 + q, n - 1)), xv, yv, zp, di);
+          f[q].bin = r.bin;
+          if (g.plain) w[q] = r.w;
+        }
+      }
+      float t[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        t[q] = tau[(i * n + min(j0 + q, n - 1)) * m + min(f[q].bin, m - 1)];
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        acc += (f[q].bin < m && j0 + q < n) ? w[q] * (double)t[q] : 0.0;
     }
   }
-  u[vox] = (float)acc;
+  if (LIT && !g.plain) {
+    const double ri = 1.0 / di;
+    acc *= ri * ri;
+  }
+  if (k0 + lane < m && (int)blockIdx.x * kNcTWaves + wv < items) u[(size_t)col * m + k] = (float)acc;
 }
 
 }  // namespace
 
-size_t nc_forward_lds_bytes(int m) { return (size_t)(kNcWaves + 1) * m * sizeof(double); }
+// Histograms, depths and columns of the forward kernel: at most 60 KiB with the counts
+// of waves and detectors that launch_nc_forward takes.
+static size_t nc_forward_lds_bytes(int m, int d, int waves) {
+  const size_t s = (m + 63) / 64;
+  return ((size_t)waves * d * nc_place(m) + 64 * s) * sizeof(double) + waves * s * kNcRow * sizeof(float);
+}
 
-hipError_t launch_nc_forward(const NcGeo& g, const float* u, float* tau, hipStream_t st) {
-  // at most (4 + 1) 1024 doubles = 40 KiB of dynamic LDS (the host limits m)
-  hipLaunchKernelGGL(k_nc_forward, dim3(g.n * g.n), dim3(kNcThreads), nc_forward_lds_bytes(g.m), st,
-                     g, u, tau);
+// Squared distances outside [1e-120, 1e120], and paths of 2^30 bins, are left
+// to the plain form.
+static bool nc_in_range(const NcGeo& g) {
+  const double zmin = 0.5 * g.range / g.m;
+  const double far = fabs(g.wall) + fabs(g.ix) + fabs(g.iy) + g.range;
+  return zmin > 1e-60 && far < 1e59 && g.cdt > 1e-60 && 4.0 * far / g.cdt < 1e9;
+}
+
+hipError_t launch_nc_forward(const NcGeo& g0, const float* u, float* tau, hipStream_t st) {
+  NcGeo g = g0;
+  g.plain = nc_in_range(g) ? 0 : 1;
+  // Two detectors per block share a voxel's illumination path, but their
+  // histograms leave room for half the waves.  Measured, one against two
+  // detectors: 24x24x224 237 / 263 us, 32x32x256 515 / 462, 45x45x300
+  // 2284 / 1985, 64x64x512 13.8 / 12.4 ms, 40x40x1000 5.9 / 8.7 ms.  Eight waves
+  // while that leaves three blocks per CU, else four (64x64x512, two detectors:
+  // 15.5 ms with eight, 12.4 with four).
+  const bool two = g.n >= 32 && g.m <= 512;
+  const int waves = 8 * (two ? 2 : 1) * nc_place(g.m) * 8 <= 48 * 1024 ? 8 : 4;
+  const int nd = g.n * g.n;
+  const int S = (g.m + 63) / 64;
+#define CNLOS_NCF(D, LIT, SM)                                                              \
+  hipLaunchKernelGGL((k_nc_forward<D, LIT, SM>), dim3((nd + D - 1) / D), dim3(64 * waves), \
+                     nc_forward_lds_bytes(g.m, D, waves), st, g, u, tau)
+#define CNLOS_NCF_S(D, LIT)                                                                \
+  do {                                                                                     \
+    if (S <= 2) CNLOS_NCF(D, LIT, 2);                                                      \
+    else if (S <= 4) CNLOS_NCF(D, LIT, 4);                                                 \
+    else if (S <= 8) CNLOS_NCF(D, LIT, 8);                                                 \
+    else CNLOS_NCF(D, LIT, 16);                                                            \
+  } while (0)
+  if (two && g.literal) CNLOS_NCF_S(2, true);
+  else if (two) CNLOS_NCF_S(2, false);
+  else if (g.literal) CNLOS_NCF_S(1, true);
+  else CNLOS_NCF_S(1, false);
+#undef CNLOS_NCF_S
+#undef CNLOS_NCF
   return hipGetLastError();
 }
 
-hipError_t launch_nc_transpose(const NcGeo& g, const float* tau, float* u, hipStream_t st) {
-  const size_t V = (size_t)g.n * g.n * g.m;
-  hipLaunchKernelGGL(k_nc_transpose, dim3((unsigned)((V + 255) / 256)), dim3(256), 0, st, g, tau, u);
+hipError_t launch_nc_transpose(const NcGeo& g0, const float* tau, float* u, hipStream_t st) {
+  NcGeo g = g0;
+  g.plain = nc_in_range(g) ? 0 : 1;
+  const int items = g.n * g.n * ((g.m + 63) / 64);
+  const dim3 grid((items + kNcTWaves - 1) / kNcTWaves), block(64 * kNcTWaves);
+  const size_t lds = (size_t)kNcTWaves * 2 * g.n * sizeof(double);
+  if (g.literal) hipLaunchKernelGGL(k_nc_transpose<true>, grid, block, lds, st, g, tau, u);
+  else hipLaunchKernelGGL(k_nc_transpose<false>, grid, block, lds, st, g, tau, u);
   return hipGetLastError();
 }
 

@@ -143,3 +143,56 @@ def test_midpoint_route_matches_the_oracle():
     got = to_host(P.volume())
     P.close()
     assert rel_l2(got, ref.u) <= 1e-3
+
+
+# bin counts around the 64-lane chunk and the histogram pad, one and two
+# detectors per block (an odd detector count leaves half a block), and the
+# launch's two wave counts; the reference sums the paths of single detectors and
+# voxels, to the same tolerance as above
+@pytest.mark.parametrize("n,m", [(5, 63), (7, 64), (9, 65), (33, 65), (33, 129), (35, 384),
+                                 (33, 512), (8, 513), (6, 1024)])
+def test_edges_of_the_launch_shapes(n, m):
+    torch = need_gpu()
+    say(f"nonconfocal edges n={n} m={m}")
+    wall, dt, illum = 0.9, 20.0 * 512 / m, (0.21, -0.13)
+    g, og = _geoms(n, m, wall, dt, illum, True)
+    u = f32(scenes.random_volume((n, n, m), 31 + n))
+    t = f32(scenes.random_signed((n, n, m), 37 + m))
+    tau = to_host(C.nc_apply(g, to_dev(torch, u)))
+    ut = to_host(C.nc_apply_T(g, to_dev(torch, t)))
+    x, z = og.lateral(), og.depth()
+    X, Y, Z = np.meshgrid(x, x, z, indexing="ij")
+    di = np.sqrt((X - illum[0]) ** 2 + (Y - illum[1]) ** 2 + Z ** 2)
+
+    def paths(i, j):
+        dd = np.sqrt((X - x[i]) ** 2 + (Y - x[j]) ** 2 + Z ** 2)
+        b = np.floor((di + dd) / og.bin_length()).astype(np.int64)
+        return np.where(b < m, b, m), 1.0 / (di * di * dd * dd)
+
+    for i, j in [(0, 0), (n - 1, n - 1), (n // 2, 1), (n - 1, 0)]:
+        b, w = paths(i, j)
+        ref = np.bincount(b.ravel(), weights=(w * u).ravel(), minlength=m + 1)[:m]
+        assert np.array_equal(tau[i, j] != 0.0, ref != 0.0)
+        assert rel_l2(tau[i, j], ref) <= TOL and max_rel(tau[i, j], ref) <= TOL
+    ref = np.zeros((n, n, m))
+    for i in range(n):
+        for j in range(n):
+            b, w = paths(i, j)
+            ref += np.where(b < m, w * t[i, j][np.minimum(b, m - 1)], 0.0)
+    assert rel_l2(ut, ref) <= TOL and max_rel(ut, ref) <= TOL
+
+
+@pytest.mark.parametrize("scale", [1e-70, 1e70])
+def test_distances_beyond_the_fast_path(scale):
+    """Geometries whose squared distances leave the reciprocal square root's
+    range take the plain arithmetic (path counts only: the weights would not
+    be FP32 values)."""
+    torch = need_gpu()
+    say(f"nonconfocal scale={scale}")
+    n, m = 6, 40
+    g, og = _geoms(n, m, 0.6 * scale, 48.0 * scale, (0.1 * scale, 0.05 * scale), False)
+    u = f32(scenes.random_volume((n, n, m), 41))
+    tau = to_host(C.nc_apply(g, to_dev(torch, u)))
+    ut = to_host(C.nc_apply_T(g, to_dev(torch, u)))
+    assert rel_l2(tau, O.apply_nonconfocal(u, og, False)) <= TOL
+    assert rel_l2(ut, O.apply_nonconfocal_T(u, og, False)) <= TOL
