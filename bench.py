@@ -522,9 +522,19 @@ def serve_workload(torch, C, scenes, n_req, rate, seed=5000, baseline=True):
 def hq_bytes(n, m, layout=False):
     """Bytes of the kernel spectrum H^ per convolution: the quarter (n + 1)^2
     of each kt plane that its evenness in kx and ky determines (the method's
-    own bytes), or the full 2n x 2n plane the plane kernel reads, lane-ordered
-    so that its loads coalesce (the layout's bytes)."""
+    own bytes), or the 2n x 2n entries per plane that the workspace holds room
+    for (the layout's bytes)."""
     return (m + 1) * (4 * n * n if layout else (n + 1) * (n + 1)) * 8
+
+
+def hq_table_bytes(n, m):
+    """Bytes of H^ that the plane kernel's table holds and a convolution reads:
+    the quarter in the order of its lanes (n >= 32), the half (n = 16, all kx)
+    or the whole plane (n = 8), for m planes."""
+    if n < 16:
+        return m * 4 * n * n * 8
+    slots = 8 if n == 16 else n // 4 + 1
+    return m * slots * (4 * n + 4) * 8
 
 
 def algorithmic_bytes(kind, n, m, dual):
@@ -912,7 +922,7 @@ def main():
     if dominant in ALU_BOUND:
         aflops = algorithmic_flops(dominant, n, m)
         achieved = aflops / (avg_us * 1e-6) / 1e12
-        layout_bytes = abytes - hq_bytes(n, m) + hq_bytes(n, m, layout=True)
+        layout_bytes = abytes - hq_bytes(n, m) + hq_table_bytes(n, m)
         roof = {"bound": "alu", "kernel": dominant,
                 "achieved": achieved, "peak": VALU_PEAK_TFLOPS,
                 "unit": "TFLOP/s", "traffic": traffic, "avg_launch_us": avg_us,

@@ -301,7 +301,8 @@ int resample_nnz(int m) {
   return 3 * m + 64;
 }
 
-// bytes of one lane-ordered H^ (every kt plane's full 2n x 2n spectrum)
+// bytes that a workspace holds for one H^: 4 n^2 entries per kt plane, the most
+// that a plane kernel's table takes (hq_pitch; the full spectrum at n = 8)
 size_t hq_bytes(const cnlos_config& c) {
   return align_up((size_t)(c.nt + 1) * 4 * c.nx * c.nx * sizeof(float2));
 }
@@ -314,7 +315,7 @@ size_t carve(cnlos_problem* p, const cnlos_config& c, uint8_t* base, bool own_hq
   const size_t V = (size_t)n * n * m;
   const size_t nn = (size_t)n * n;
   const size_t nspec = (size_t)(m + 1) * nn;
-  // H^: the full 2n x 2n spectrum of every kt plane, lane-ordered
+  // H^: room for the full 2n x 2n spectrum of every kt plane (hq_bytes)
   const size_t nhq = (size_t)(m + 1) * 4 * n * n;
   DevCtl* ctl = cv.take<DevCtl>(1);
   double* partials = cv.take<double>((size_t)SL_COUNT * kMaxBlocks);

@@ -290,8 +290,8 @@ struct Tables {
   ResampleTables S;
   const float* sig_xy;    // 4 sin^2(pi k / n), k < n
   const float* sig_t;     // 4 sin^2(pi k / m), k <= m/2
-  const float2* hq;       // H^: [m+1] planes of 4 n^2 entries, lane-ordered for the
-                          // plane kernel that reads them (hq_lane_index)
+  const float2* hq;       // H^: [m+1] planes of hq_pitch entries, in the order in which
+                          // the plane kernel's lanes read them (hq_store)
   Plan plan;
 };
 

@@ -13,10 +13,11 @@
 // kt = 0..m necessary (the two real bins kt = 0, m share one plane);
 // the (x, y) padding to 2n x 2n lives only inside the plane kernel: rows and
 // columns are transformed with their zero halves folded into twists, and the
-// n x n crop is taken before anything leaves the CU (n = 128 splits the plane
-// by ky parity to fit LDS).
+// n x n crop is taken before anything leaves the CU (n = 128 takes the ky
+// parities one after the other to fit LDS).
 #include "cnlos_internal.h"
 #include "fft_device.h"
+#include "fft_quad.h"
 #include "stencil_device.h"
 
 namespace cnlos {
@@ -510,13 +511,13 @@ k_tinv_conv(const float2* __restrict__ spec, int nn, ResampleTables S,
 }
 
 // ---------------------------------------------------------------------------
-// Register-resident plane kernel of the convolution (n <= 64).  Rows: 8 lanes
-// per row transform the zero-padded row (length 2n) with the upper half of
-// the first stage folded into a twist; the 2n spectrum positions go to LDS.
-// Columns: 8 lanes per spectrum column transform the zero-padded column,
-// multiply by H^ (or its conjugate) at the position's frequency, transform
-// back and keep the first n rows.  Rows again: inverse, keep the first n.
-// LDS is touched three times per element; every butterfly runs in registers.
+// Plane kernel of the convolution on eight-lane transforms, for n = 8 (where
+// four lanes would hold two values each; larger planes: k_plane_conv_quad).
+// Rows: 8 lanes per row transform the zero-padded row (length 2n) with the upper
+// half of the first stage folded into a twist; the 2n spectrum positions go to
+// LDS.  Columns: 8 lanes per spectrum column transform the zero-padded column,
+// multiply by H^ (or its conjugate) at the position's frequency, transform back
+// and keep the first n rows.  Rows again: inverse, keep the first n.
 //
 // Block 0 holds the two real planes kt = 0 and kt = m packed as
 // Z = P_0 + i P_m.  H^ is real on both (h is even in x and y, and the t phase
@@ -524,9 +525,10 @@ k_tinv_conv(const float2* __restrict__ spec, int nn, ResampleTables S,
 // separates with the partner frequency -k (see plane_conv_cols_packed); the
 // result is conv(P_0) + i conv(P_m).
 // ---------------------------------------------------------------------------
-// YS: LDS row stride of the transposes, L + PAD.  The pad changes only where
-// values sit in LDS (bank conflicts of the column accesses), never a result;
-// the plan picks it per shape (1, 2 or 4; 2 when untuned).
+// YS: LDS row stride of the transposes, L + PAD (here and in QuadCfg's kernels).
+// The pad changes only where values sit in LDS (bank conflicts of the column
+// accesses), never a result; the plan picks it per shape (1, 2 or 4; 2 when
+// untuned).
 template <int LOGN>
 struct PlaneRegCfg {
   static constexpr int N = 1 << LOGN, L = 2 * N, NT = 8 * N;
@@ -692,310 +694,426 @@ k_plane_conv_reg(float2* __restrict__ spec, const float2* __restrict__ hq,
   }
 }
 
-// Plane kernel of the convolution for n = 128, where one padded 2n x 2n
-// plane does not fit in LDS.  The padded transform is split by the parity h
-// of ky: the even and odd ky rows of the spectrum are n-point transforms of
-// each row (the odd ones after the twist W_2n^y), so each half is
-//   rows:    n-point DIF per row (twisted for h = 1) -> LDS [x][ky_h]
-//   columns: zero-padded 2n-point transform per ky_h column, times H^ (or its
-//            conjugate), inverse, keep the first n rows
-//   rows:    n-point DIT back (untwisted for h = 1), accumulated in registers
-// and the sum over both halves is the cropped padded convolution.  A lane
-// group of 8 handles two rows / columns in turn.  Block 0 holds the packed
-// real planes kt = 0 and kt = m (half_cols_packed), so the launch has m
-// blocks, whole rounds of one block per CU.
-template <int LOGN, int PAD = 2>
-struct PlaneHalfCfg {
-  static constexpr int N = 1 << LOGN, L = 2 * N, NT = 4 * N, G = NT / 8;
-  static constexpr int RN = N / 8, YS = N + PAD;   // row stride (pad as in PlaneRegCfg)
+// ---------------------------------------------------------------------------
+// Plane kernels of the convolution for n >= 16, on the four-lane transforms of
+// fft_quad.h: 16 rows or columns per wave, both zero-padded transforms as two
+// halves by the parity of ky and kx.
+//
+// H^ in memory.  H^ is even in kx and ky.  A lane group takes the columns ky
+// and -ky (n <= 64), or the two columns' groups read the same entries (n =
+// 128), and -kx sits in the lane of kx, so the table holds the quarter 0 <= kx,
+// ky <= n once: [slot][ky pair][lane group], in the order in which a wave's
+// loads read 64 consecutive entries, then the column ky = n (n = 16, where -kx
+// is in another lane: all kx, [slot] per register).
+template <int LOGN>
+struct QuadCfg {
+  static constexpr int N = 1 << LOGN, L = 2 * N, E = N / 4, NT = 4 * N;
+  // kernel values per lane and half, and per plane
+  static constexpr int S0 = E == 4 ? 4 : E / 2 + 1, S1 = E == 4 ? 4 : E / 2, SLOTS = S0 + S1;
+  static constexpr int PITCH = SLOTS * (4 * N + 4);
+  static constexpr int EXTRA = SLOTS * 4 * N;           // the column ky = n: [slot][g]
 };
+// entries of one kt plane of H^
+constexpr int hq_pitch(int logn) {
+  return logn == 4   ? QuadCfg<4>::PITCH
+         : logn == 5 ? QuadCfg<5>::PITCH
+         : logn == 6 ? QuadCfg<6>::PITCH
+         : logn == 7 ? QuadCfg<7>::PITCH
+                     : 4 << (2 * logn);
+}
+static_assert(QuadCfg<4>::PITCH <= 4 << 8 && QuadCfg<7>::PITCH <= 4 << 14,
+              "a plane of H^ within the 4 n^2 entries that the workspace holds");
 
-// rows of the half-split plane kernel: forward n-point DIF of the two rows
-// of a lane group (twisted by W_2n^y for the odd half) into LDS
-template <int LOGN, int PAD>
-__device__ __forceinline__ void half_rows_fwd(float2 (&v)[2][PlaneHalfCfg<LOGN>::RN], int h,
-                                              float2* Y, const float2* tws, const float2* twc,
-                                              int g, int s) {
-  using PC = PlaneHalfCfg<LOGN, PAD>;
-  constexpr int RN = PC::RN, YS = PC::YS, G = PC::G;
+// element o of q: a 32-bit offset from a base that is the same for the wave
+// (one address register per access instead of two)
+__device__ __forceinline__ float2 at32(const float2* __restrict__ q, uint32_t o) {
+  return *reinterpret_cast<const float2*>(reinterpret_cast<const char*>(q) + (o << 3));
+}
+__device__ __forceinline__ void put32(float2* __restrict__ q, uint32_t o, float2 v) {
+  *reinterpret_cast<float2*>(reinterpret_cast<char*>(q) + (o << 3)) = v;
+}
+// elements n2 = C of a lane's row part, x[4 i + C], from and to memory (16-byte
+// accesses from E = 8 on: the E/4 elements are neighbours, 16-byte aligned)
+template <int E>
+__device__ __forceinline__ void row_get(float2 (&x)[E], const float2* __restrict__ q, uint32_t p0,
+                                        int c) {
+  if constexpr (E == 4) {
+    x[c] = at32(q, p0 + E * c);
+  } else {
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    if (h) {
-#pragma unroll
-      for (int r = 0; r < RN; ++r) v[i][r] = cmul(v[i][r], tws[8 * r + s]);
+    for (int i = 0; i < E / 4; i += 2) {
+      const float4 v = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(q) +
+                                                        ((p0 + E * c + i) << 3));
+      x[4 * i + c] = make_float2(v.x, v.y);
+      x[4 * i + 4 + c] = make_float2(v.z, v.w);
     }
-    dif_inlane<8, RN, RN / 2>(v[i], s, twc);
-    dif_xlane<8, RN>(v[i], s, twc);
+  }
+}
+template <int E>
+__device__ __forceinline__ void row_put(const float2 (&x)[E], float2* __restrict__ q, uint32_t p0,
+                                        int c) {
+  if constexpr (E == 4) {
+    put32(q, p0 + E * c, x[c]);
+  } else {
 #pragma unroll
-    for (int r = 0; r < RN; ++r) Y[(g + G * i) * YS + 8 * r + s] = v[i][r];
+    for (int i = 0; i < E / 4; i += 2)
+      *reinterpret_cast<float4*>(reinterpret_cast<char*>(q) + ((p0 + E * c + i) << 3)) =
+          make_float4(x[4 * i + c].x, x[4 * i + c].y, x[4 * i + 4 + c].x, x[4 * i + 4 + c].y);
+  }
+}
+// this lane's kernel values of half H, from place `first` of the plane on
+template <int LOGN, int H>
+__device__ __forceinline__ void quad_hq_load(float2 (&hs)[QuadCfg<LOGN>::S0],
+                                             const float2* __restrict__ hp, uint32_t first,
+                                             uint32_t stride) {
+  using QC = QuadCfg<LOGN>;
+  constexpr int B = H ? QC::S0 : 0, CNT = H ? QC::S1 : QC::S0;
+#pragma unroll
+  for (int s = 0; s < CNT; ++s) hs[s] = at32(hp, first + (B + s) * stride);
+}
+// the value of register (i, k2)
+template <int E, int H, int S>
+__device__ __forceinline__ float2 quad_hq(const float2 (&hs)[S], int i, int k2, int g) {
+  if constexpr (E == 4) {
+    return hs[k2];
+  } else {
+    const int t = 4 * (i >> 1);
+    if (H == 1 || t > 0) return hs[t + ((i & 1) ? 3 - k2 : k2)];
+    // lane 0: k1 = 0 (i = 0, its k2 = 1 and 3 are negatives) and k1 = E/2
+    const bool z = g == 0;
+    auto sel = [&](int a, int b) {
+      return make_float2(z ? hs[a].x : hs[b].x, z ? hs[a].y : hs[b].y);
+    };
+    if (i == 0) return k2 == 3 ? sel(1, 3) : hs[k2];
+    return k2 == 0 ? hs[3] : k2 == 1 ? sel(S - 1, 2) : k2 == 2 ? sel(S - 1, 1) : sel(3, 0);
+  }
+}
+template <int LOGN, bool ADJ, int H>
+__device__ __forceinline__ void quad_product(float2 (&c)[QuadCfg<LOGN>::E],
+                                             const float2 (&hs)[QuadCfg<LOGN>::S0], int g) {
+  constexpr int E = QuadCfg<LOGN>::E;
+#pragma unroll
+  for (int r = 0; r < E; ++r) {
+    const float2 h = quad_hq<E, H>(hs, r >> 2, r & 3, g);
+    c[r] = ADJ ? cmulc(c[r], h) : cmul(c[r], h);
+  }
+}
+// Block 0 holds the two real planes kt = 0 and kt = m packed as P_0 + i P_m;
+// H^ is real on both, and the product separates with the partner frequency
+// (-kx, -ky):  Y(k) = Z(k) (H_0 + H_m)/2 + conj(Z(-k)) (H_0 - H_m)/2, the
+// spectrum of conv(P_0) + i conv(P_m).  Plane 0 of H^ holds the two factors as
+// one pair (k_hq_pack_real).
+__device__ __forceinline__ float2 quad_pair_product(float2 own, float2 par, float2 ab) {
+  return make_float2(ab.x * own.x + ab.y * par.x, ab.x * own.y - ab.y * par.y);
+}
+// place in a column's spectrum (stored at [4 r + g], r = 4 i + k2) of the
+// negative of register n of half H
+template <int E, int H>
+__device__ __forceinline__ int quad_negative(int n, int g) {
+  const int i = n >> 2, k2 = n & 3;
+  if constexpr (E == 4) {
+    if (H) return 4 * (3 - k2) + 3 - g;
+    return 4 * (g ? 3 - k2 : (4 - k2) & 3) + ((4 - g) & 3);
+  } else {
+    const int np = 4 * (i ^ 1) + 3 - k2;
+    if (H == 1 || i > 1) return 4 * np + g;
+    return 4 * (g ? np : 4 * i + (i ? 3 - k2 : (4 - k2) & 3)) + g;
   }
 }
 
-// columns of the half-split plane kernel: padded 2n-point transform of each
-// ky_h column, H^ product, inverse, first n rows back to LDS
+// A lane group's columns of a plane (one, or a column and its negative), in
+// place in LDS (element 4 n + g at Yc[4 n YS]): both kx halves forward, product,
+// inverse, summed.  The kernel values of a half are read before its transform,
+// which hides their latency; the two columns share them unless `apart` (the
+// columns 0 and n; the same for a wave).
+// PACKED (block 0; every thread of the block takes part): the partner column's
+// spectrum half, at Yp, has as many values as that column has places in Y.
+template <int LOGN, bool ADJ, int YS, bool PACKED, int NC, typename Fn>
+__device__ __forceinline__ void quad_columns(float2* const (&Yc)[NC], const float2* const (&Yp)[NC],
+                                             const float2* Hp, const uint32_t (&h0)[NC],
+                                             const uint32_t (&hst)[NC], bool apart,
+                                             const float2* tw2, int g, Fn before_last) {
+  using QC = QuadCfg<LOGN>;
+  constexpr int E = QC::E;
+  float2 c[PACKED ? NC : 1][E], r[NC][E], in[PACKED ? NC : 1][PACKED ? E : 1];
+  if constexpr (PACKED) {
+#pragma unroll
+    for (int k = 0; k < NC; ++k)
+#pragma unroll
+      for (int n = 0; n < E; ++n) in[k][n] = Yc[k][4 * n * YS];
+  }
+  auto kx_half = [&](auto hc) {
+    constexpr int H = decltype(hc)::value;
+    float2 hs[QC::S0];
+    if constexpr (!PACKED) {
+      quad_hq_load<LOGN, H>(hs, Hp, h0[0], hst[0]);
+#pragma unroll
+      for (int k = 0; k < NC; ++k) {
+#pragma unroll
+        for (int n = 0; n < E; ++n) c[0][n] = Yc[k][4 * n * YS];
+        if (k > 0 && apart) quad_hq_load<LOGN, H>(hs, Hp, h0[k], hst[k]);
+        quad_group_end<E>();
+        quad_col_fwd<E, H>(c[0], tw2, g);
+        quad_group_end<E>();
+        quad_product<LOGN, ADJ, H>(c[0], hs, g);
+        if constexpr (H == 1) before_last();
+        quad_group_end<E>();
+        quad_col_inv<E, H>(c[0], tw2, g);
+#pragma unroll
+        for (int n = 0; n < E; ++n) r[k][n] = H ? cadd(r[k][n], c[0][n]) : c[0][n];
+        quad_group_end<E>();
+      }
+    } else {
+#pragma unroll
+      for (int k = 0; k < NC; ++k) {
+#pragma unroll
+        for (int n = 0; n < E; ++n) c[k][n] = in[k][n];
+        quad_col_fwd<E, H>(c[k], tw2, g);
+#pragma unroll
+        for (int n = 0; n < E; ++n) Yc[k][4 * n * YS] = c[k][n];
+      }
+      __syncthreads();
+#pragma unroll
+      for (int k = 0; k < NC; ++k) {
+        quad_hq_load<LOGN, H>(hs, Hp, h0[k], hst[k]);
+#pragma unroll
+        for (int n = 0; n < E; ++n)
+          c[k][n] = quad_pair_product(c[k][n], Yp[k][quad_negative<E, H>(n, g) * YS],
+                                      quad_hq<E, H>(hs, n >> 2, n & 3, g));
+      }
+      __syncthreads();
+      if constexpr (H == 1) before_last();
+#pragma unroll
+      for (int k = 0; k < NC; ++k) {
+        quad_col_inv<E, H>(c[k], tw2, g);
+#pragma unroll
+        for (int n = 0; n < E; ++n) r[k][n] = H ? cadd(r[k][n], c[k][n]) : c[k][n];
+      }
+    }
+  };
+  kx_half(std::integral_constant<int, 0>{});
+  kx_half(std::integral_constant<int, 1>{});
+#pragma unroll
+  for (int k = 0; k < NC; ++k)
+#pragma unroll
+    for (int n = 0; n < E; ++n) Yc[k][4 * n * YS] = r[k][n];
+}
+
+// n <= 64: a block per kt plane, Y [n][2 n] with the even ky first.  Bound by
+// vector issue (64x64x512: 80 % of the SIMDs' cycles, 0.58 of the instructions
+// of the eight-lane form, whose cross-lane stages took half of them).
+// SPLIT = 1 (n = 64): 4 n threads; a lane group takes both ky halves of its row
+// and the columns ky and -ky.  SPLIT = 2 (n <= 32): 8 n threads; the second half
+// of the waves takes the odd ky and the columns -ky, and the two halves of a
+// row's sum meet in LDS: twice the waves with half the chain each, for planes
+// too small to fill a CU (32x32x256: 7.0 against 8.6 us per pass; at n = 64,
+// where two blocks per CU already do, 25.1 against 23.6).
+template <int LOGN>
+constexpr int quad_split() { return LOGN < 6 ? 2 : 1; }
 template <int LOGN, bool ADJ, int PAD>
-__device__ __forceinline__ void half_cols(int h, float2* Y, const float2* Hp, const float2* tws,
-                                          const float2* twc, int g, int s) {
-  using PC = PlaneHalfCfg<LOGN, PAD>;
-  constexpr int N = PC::N, YS = PC::YS, G = PC::G;
-  constexpr int RE = PlaneRegCfg<LOGN>::RE;
-#pragma unroll 1
-  for (int i = 0; i < 2; ++i) {
-    const int col = g + G * i;
-    // H^ (lane-ordered: a wave's load reads 64 consecutive entries) in chunks
-    // of 8, so that its loads do not all stay live at once; the first chunk
-    // is loaded before the forward transform and each next one before the
-    // products of the current one, so that their latency is hidden
-    const float2* Hh = Hp + ((size_t)h * RE * N + col) * 8 + s;
-    float2 hc[8];
-#pragma unroll
-    for (int r = 0; r < 8; ++r) hc[r] = Hh[r * N * 8];
-    float2 c[RE];
-#pragma unroll
-    for (int r = 0; r < RE / 2; ++r) c[r] = Y[(8 * r + s) * YS + col];
-    col_fwd<LOGN>(c, s, tws, twc);
-#pragma unroll
-    for (int r0 = 0; r0 < RE; r0 += 8) {
-      float2 hn[8];
-      if (r0 + 8 < RE) {
-#pragma unroll
-        for (int r = 0; r < 8; ++r) hn[r] = Hh[(r0 + 8 + r) * N * 8];
-      }
-#pragma unroll
-      for (int r = 0; r < 8; ++r) c[r0 + r] = ADJ ? cmulc(c[r0 + r], hc[r]) : cmul(c[r0 + r], hc[r]);
-      __builtin_amdgcn_sched_barrier(0);
-      if (r0 + 8 < RE) {
-#pragma unroll
-        for (int r = 0; r < 8; ++r) hc[r] = hn[r];
-      }
-    }
-    col_inv<LOGN>(c, s, tws, twc);
-#pragma unroll
-    for (int r = 0; r < RE / 2; ++r) Y[(8 * r + s) * YS + col] = c[r];
-  }
-}
-
-// bits of x reversed within `bits` (a constant after unrolling)
-__device__ __forceinline__ constexpr int rev_bits(int x, int bits) {
-  int y = 0;
-  for (int i = 0; i < bits; ++i) y |= ((x >> i) & 1) << (bits - 1 - i);
-  return y;
-}
-
-// Columns of block 0 of the half-split plane kernel, which holds the two real
-// planes kt = 0 and kt = m packed as Z = P_0 + i P_m.  As in
-// plane_conv_cols_packed, each spectrum position combines its own value with
-// the partner at (-kx, -ky):
-//   Y(k) = Z^(k) (H_0 + H_m)/2 + conj(Z^(-k)) (H_0 - H_m)/2
-// (the two factors as one pair in plane 0 of H^).  Negating ky keeps its
-// parity, so the partner column lies in the same half; a lane group takes a
-// column A and its partner B (ky_h and n - ky_h for h = 0, n - 1 - ky_h for
-// h = 1; group 0 of the even half the two self-partnered columns 0 and n/2).
-// In a column, position 8r + s holds kx = brev(8r + s); -kx sits at register
-// r' = brev(2^b - brev(r)) (b bits of r; r' = 0 for r = 0) and lane 7 - s, or
-// for r = 0 at the lane whose reversed index is -brev3(s) mod 8.  r and r'
-// share their highest set bit, so the lower and the upper half of the
-// registers pair only within themselves.
-// Registers hold one column spectrum per transform: A's spectrum (2n
-// entries) waits in the n LDS slots of A and the n of B while B is
-// transformed, and A's combined spectrum again while B is transformed back.
-template <int LOGN, int PAD>
-__device__ __forceinline__ void half_cols_packed(int h, float2* Y, const float2* Hab,
-                                                 const float2* tws, const float2* twc, int g,
-                                                 int s) {
-  using PC = PlaneHalfCfg<LOGN, PAD>;
-  constexpr int N = PC::N, YS = PC::YS;
-  constexpr int RE = PlaneRegCfg<LOGN>::RE, RH = RE / 2, LR = LOGN + 1 - 3;
-  const bool self = h == 0 && g == 0;
-  const int ka = g, kb = self ? N / 2 : (h == 0 ? N - g : N - 1 - g);
-  const int colA = brev(ka, LOGN), colB = brev(kb, LOGN);
-  auto slot = [&](int r, int col) -> float2& { return Y[(8 * r + s) * YS + col]; };
-  // A forward: upper half to A's slots; lower half to B's once B is loaded
-  float2 c[RE];
-  {
-    float2 a[RE];
-#pragma unroll
-    for (int r = 0; r < RH; ++r) a[r] = slot(r, colA);
-    col_fwd<LOGN>(a, s, tws, twc);
-#pragma unroll
-    for (int r = 0; r < RH; ++r) slot(r, colA) = a[r + RH];
-#pragma unroll
-    for (int r = 0; r < RH; ++r) c[r] = slot(r, colB);
-#pragma unroll
-    for (int r = 0; r < RH; ++r) slot(r, colB) = a[r];
-  }
-  col_fwd<LOGN>(c, s, tws, twc);                   // B's spectrum in registers
-  const float2* HA = Hab + ((size_t)h * RE * N + colA) * 8 + s;
-  const float2* HB = Hab + ((size_t)h * RE * N + colB) * 8 + s;
-  const int lane = threadIdx.x & 63, base = lane & ~7;
-  const int s0 = brev((8 - brev(s, 3)) & 7, 3);            // partner lane of register 0
-  // value of the partner position of register r: lane s ^ 7, or s0 for r = 0
-  auto par = [&](float2 v, int r) {
-    const int src = base | (r == 0 ? s0 : (s ^ 7));
-    return make_float2(__shfl(v.x, src, 64), __shfl(v.y, src, 64));
-  };
-  auto comb = [&](float2 own, float2 pv, float2 ab) {
-    return make_float2(ab.x * own.x + ab.y * pv.x, ab.x * own.y - ab.y * pv.y);
-  };
-  // combine the registers r0 .. r0 + RH - 1 of A (aa) and B (c) in place,
-  // pair by pair; the partner column of A is B, of B is A (each itself in
-  // group 0 of the even half)
-  float2 ua[RH], la[RH];
-  auto combine = [&](float2 (&aa)[RH], int r0) {
-#pragma unroll
-    for (int i = 0; i < RH; ++i) {
-      const int r = r0 + i;
-      const int rp = r == 0 ? 0 : rev_bits((RE - rev_bits(r, LR)) & (RE - 1), LR);
-      const int ip = rp - r0;
-      if (ip < i) continue;                        // the pair was done at r' (static)
-      const float2 pA_r = par(self ? aa[ip] : c[rp], r), pA_rp = par(self ? aa[i] : c[r], rp);
-      const float2 pB_r = par(self ? c[rp] : aa[ip], r), pB_rp = par(self ? c[r] : aa[i], rp);
-      const float2 nA_r = comb(aa[i], pA_r, HA[r * N * 8]);
-      const float2 nB_r = comb(c[r], pB_r, HB[r * N * 8]);
-      if (ip != i) {
-        const float2 nA_rp = comb(aa[ip], pA_rp, HA[rp * N * 8]);
-        const float2 nB_rp = comb(c[rp], pB_rp, HB[rp * N * 8]);
-        aa[ip] = nA_rp;
-        c[rp] = nB_rp;
-      }
-      aa[i] = nA_r;
-      c[r] = nB_r;
-      // one pair's H^ loads and shuffles at a time (no hoisting of all of them)
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  };
-#pragma unroll
-  for (int r = 0; r < RH; ++r) ua[r] = slot(r, colA);
-  combine(ua, RH);
-#pragma unroll
-  for (int r = 0; r < RH; ++r) la[r] = slot(r, colB);
-  combine(la, 0);
-  // A's combined spectrum to the slots, B back, then A back
-#pragma unroll
-  for (int r = 0; r < RH; ++r) {
-    slot(r, colA) = la[r];
-    slot(r, colB) = ua[r];
-  }
-  col_inv<LOGN>(c, s, tws, twc);
-  float2 ob[RH];
-#pragma unroll
-  for (int r = 0; r < RH; ++r) ob[r] = c[r];
-  {
-    float2 a[RE];
-#pragma unroll
-    for (int r = 0; r < RH; ++r) {
-      a[r] = slot(r, colA);
-      a[r + RH] = slot(r, colB);
-    }
-#pragma unroll
-    for (int r = 0; r < RH; ++r) slot(r, colB) = ob[r];
-    col_inv<LOGN>(a, s, tws, twc);
-#pragma unroll
-    for (int r = 0; r < RH; ++r) slot(r, colA) = a[r];
-  }
-}
-
-// inverse rows: n-point DIT of a row from LDS (untwisted for the odd half)
-template <int LOGN, int PAD>
-__device__ __forceinline__ void half_row_inv(float2 (&v)[PlaneHalfCfg<LOGN>::RN], int h, int x,
-                                             const float2* Y, const float2* tws, const float2* twc,
-                                             int s) {
-  using PC = PlaneHalfCfg<LOGN, PAD>;
-  constexpr int RN = PC::RN, YS = PC::YS;
-#pragma unroll
-  for (int r = 0; r < RN; ++r) v[r] = Y[x * YS + 8 * r + s];
-  dit_xlane<8, RN>(v, s, twc);
-  dit_inlane<8, RN, RN / 2>(v, s, twc);
-  if (h) {
-#pragma unroll
-    for (int r = 0; r < RN; ++r) v[r] = cmulc(v[r], tws[8 * r + s]);
-  }
-}
-
-// One plane through the half-split transform: per ky half, rows forward,
-// columns (PACKED: block 0's pairs of partner columns, else the H^ product),
-// rows back, the odd half accumulated onto the even one.
-template <int LOGN, bool ADJ, bool PACKED, int PAD>
-__device__ __forceinline__ void plane_half_body(float2* __restrict__ P, const float2* Hp,
-                                                float2* Y, float2* tws, float2* twc, float2 tv_s,
-                                                float2 tv_c, int g, int s) {
-  using PC = PlaneHalfCfg<LOGN>;
-  constexpr int N = PC::N, L = PC::L, G = PC::G, RN = PC::RN;
-  // even ky half; each thread owns plane elements (g + G i, 8 r + s) throughout
-  float2 v[2][RN];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int r = 0; r < RN; ++r) v[i][r] = P[(g + G * i) * N + 8 * r + s];
-  {
-    const int tid = threadIdx.x;
-    tws[tid % N] = tv_s;
-    twc[tid % L] = tv_c;
-  }
-  __syncthreads();
-  half_rows_fwd<LOGN, PAD>(v, 0, Y, tws, twc, g, s);
-  __syncthreads();
-  if constexpr (PACKED) half_cols_packed<LOGN, PAD>(0, Y, Hp, tws, twc, g, s);
-  else half_cols<LOGN, ADJ, PAD>(0, Y, Hp, tws, twc, g, s);
-  __syncthreads();
-  // the odd half's input, then the even half's output in its place
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int r = 0; r < RN; ++r) v[i][r] = P[(g + G * i) * N + 8 * r + s];
-#pragma unroll 1
-  for (int i = 0; i < 2; ++i) {
-    float2 o[RN];
-    half_row_inv<LOGN, PAD>(o, 0, g + G * i, Y, tws, twc, s);
-#pragma unroll
-    for (int r = 0; r < RN; ++r) P[(g + G * i) * N + 8 * r + s] = o[r];
-  }
-  __syncthreads();                                 // Y is rewritten by the odd half
-  half_rows_fwd<LOGN, PAD>(v, 1, Y, tws, twc, g, s);
-  __syncthreads();
-  if constexpr (PACKED) half_cols_packed<LOGN, PAD>(1, Y, Hp, tws, twc, g, s);
-  else half_cols<LOGN, ADJ, PAD>(1, Y, Hp, tws, twc, g, s);
-  __syncthreads();
-#pragma unroll 1
-  for (int i = 0; i < 2; ++i) {
-    float2 o[RN];
-    half_row_inv<LOGN, PAD>(o, 1, g + G * i, Y, tws, twc, s);
-#pragma unroll
-    for (int r = 0; r < RN; ++r) {
-      float2* q = P + (g + G * i) * N + 8 * r + s;
-      *q = cadd(*q, o[r]);
-    }
-  }
-}
-
-template <int LOGN, bool ADJ, int PAD>
-__global__ void __launch_bounds__(PlaneHalfCfg<LOGN>::NT)
-k_plane_conv_half(float2* __restrict__ spec, const float2* __restrict__ hq,
-                  const float2* __restrict__ tw, const float2* __restrict__ twcg, const DevCtl* ctl,
-                  size_t zs, size_t hzs, int gate) {
-  using PC = PlaneHalfCfg<LOGN, PAD>;
-  constexpr int N = PC::N, L = PC::L, NT = PC::NT, G = PC::G, YS = PC::YS;
-  static_assert(2 * G == N, "two rows per lane group");
+__global__ void __launch_bounds__(quad_split<LOGN>() * QuadCfg<LOGN>::NT, 2 * quad_split<LOGN>())
+k_plane_conv_quad(float2* __restrict__ spec, const float2* __restrict__ hq,
+                  const float2* __restrict__ tw, const DevCtl* ctl, size_t zs, size_t hzs,
+                  int gate) {
+  using QC = QuadCfg<LOGN>;
+  constexpr int N = QC::N, L = QC::L, E = QC::E, YS = L + PAD;
+  constexpr bool SPLIT = quad_split<LOGN>() == 2;
   __shared__ float2 Y[N * YS];
-  __shared__ float2 tws[N];
-  __shared__ float2 twc[L];
+  __shared__ float2 tw2[L];
   const size_t zo = (size_t)blockIdx.z * zs;
   ctl = zsh(ctl, zo);
   if (gated_off(ctl, gate)) return;
   spec = zsh(spec, zo);
   hq = zsh(hq, (size_t)blockIdx.z * hzs);   // 0: one H^ for every scene
   tw = zsh(tw, zo);
-  twcg = zsh(twcg, zo);
-  const int tid = threadIdx.x, g = tid >> 3, s = tid & 7;
+  const int tid = threadIdx.x, j = tid & 15, g = (tid >> 4) & 3;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const bool second = SPLIT && wv >= N / 16;         // the same for a wave
+  const int row = (16 * wv + j) & (N - 1);
   float2* P = spec + (size_t)blockIdx.x * N * N;
-  const float2* Hp = hq + (size_t)blockIdx.x * L * L;     // lane-ordered H^ of this plane
-  // twiddle tables: every thread copies the entry of its index modulo the
-  // table size (NT >= L >= N), in the same round trip as the first rows
-  const float2 tv_s = tw[tid % N], tv_c = twcg[tid % L];
-  // block 0: the packed real planes kt = 0 and kt = m, a separate path so that
-  // its register demand does not weigh on the other blocks' code
-  if (blockIdx.x == 0) plane_half_body<LOGN, ADJ, true, PAD>(P, Hp, Y, tws, twc, tv_s, tv_c, g, s);
-  else plane_half_body<LOGN, ADJ, false, PAD>(P, Hp, Y, tws, twc, tv_s, tv_c, g, s);
+  const uint32_t p0 = row * N + (E / 4) * g;
+  const float2* Hp = hq + (size_t)blockIdx.x * QC::PITCH;
+  // the block's rows and the twiddles in one round trip; W_2N^(t + N) = -W_2N^t
+  float2 x[E], v[E];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) row_get<E>(x, P, p0, c);
+  {
+    const int t = tid & (L - 1);
+    const float2 tv = tw[t & (N - 1)];
+    tw2[t] = t < N ? tv : make_float2(-tv.x, -tv.y);
+  }
+  __syncthreads();
+  float2* Yr = Y + row * YS + g;                     // even ky 2 (4 k + g) at Yr[4 k], odd at + N
+  if (!second) {
+    quad_row_fwd<E, 0>(x, v, tw2, g);
+#pragma unroll
+    for (int k = 0; k < E; ++k) Yr[4 * k] = v[k];
+  }
+  if (!SPLIT || second) {
+    quad_row_fwd<E, 1>(x, v, tw2, g);
+#pragma unroll
+    for (int k = 0; k < E; ++k) Yr[N + 4 * k] = v[k];
+  }
+  __syncthreads();
+  // pair `row` of columns: even ky = 2 q with 2 (n - q) (0 with n), odd ky =
+  // 2 q + 1 with 2 (n - 1 - q) + 1
+  {
+    const int odd = row >= N / 2 ? 1 : 0, q = row & (N / 2 - 1);
+    const int ca = odd * N + q, cb = odd * N + (odd ? N - 1 - q : (q ? N - q : N / 2));
+    const bool self = row == 0;
+    const uint32_t ha = tid & (4 * N - 1), hb = self ? QC::EXTRA + g : ha;
+    const uint32_t sb = self ? 4 : 4 * N;
+    float2* Yg = Y + g * YS;
+    if constexpr (SPLIT) {
+      float2* const Yc[1] = {Yg + (second ? cb : ca)};
+      const float2* const Yp[1] = {Y + (second != self ? ca : cb)};
+      const uint32_t h0[1] = {second ? hb : ha}, st[1] = {second ? sb : 4u * N};
+      if (blockIdx.x == 0)
+        quad_columns<LOGN, ADJ, YS, true, 1>(Yc, Yp, Hp, h0, st, true, tw2, g, [] {});
+      else
+        quad_columns<LOGN, ADJ, YS, false, 1>(Yc, Yp, Hp, h0, st, true, tw2, g, [] {});
+    } else {
+      float2* const Yc[2] = {Yg + ca, Yg + cb};
+      const float2* const Yp[2] = {Y + (self ? ca : cb), Y + (self ? cb : ca)};
+      const uint32_t h0[2] = {ha, hb}, st[2] = {4u * N, sb};
+      if (blockIdx.x == 0)
+        quad_columns<LOGN, ADJ, YS, true, 2>(Yc, Yp, Hp, h0, st, true, tw2, g, [] {});
+      else
+        quad_columns<LOGN, ADJ, YS, false, 2>(Yc, Yp, Hp, h0, st, wv == 0, tw2, g, [] {});
+    }
+  }
+  __syncthreads();
+  if constexpr (!SPLIT) {
+#pragma unroll
+    for (int k = 0; k < E; ++k) v[k] = Yr[4 * k];
+    quad_row_inv<E, 0, false>(v, x, tw2, g);
+#pragma unroll
+    for (int k = 0; k < E; ++k) v[k] = Yr[N + 4 * k];
+    quad_row_inv<E, 1, true>(v, x, tw2, g);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) row_put<E>(x, P, p0, c);
+  } else {
+    // each half's inverse, then their sum: a lane group gives half of its
+    // elements to the other half's group through its own places in Y
+    float2* Ym = Yr + (second ? N : 0);
+    const float2* Yo = Yr + (second ? 0 : N);
+#pragma unroll
+    for (int k = 0; k < E; ++k) v[k] = Ym[4 * k];
+    if (second) quad_row_inv<E, 1, false>(v, x, tw2, g);
+    else quad_row_inv<E, 0, false>(v, x, tw2, g);
+    auto give = [&](auto sc) {                         // elements n2 = C, C + 1
+      constexpr int C = decltype(sc)::value;
+#pragma unroll
+      for (int c = C; c < C + 2; ++c)
+#pragma unroll
+        for (int i = 0; i < E / 4; ++i) Ym[4 * (4 * i + c)] = x[4 * i + c];
+    };
+    auto finish = [&](auto sc) {
+      constexpr int C = decltype(sc)::value;
+#pragma unroll
+      for (int c = C; c < C + 2; ++c) {
+#pragma unroll
+        for (int i = 0; i < E / 4; ++i) x[4 * i + c] = cadd(x[4 * i + c], Yo[4 * (4 * i + c)]);
+        row_put<E>(x, P, p0, c);
+      }
+    };
+    if (second) give(std::integral_constant<int, 0>{});
+    else give(std::integral_constant<int, 2>{});
+    __syncthreads();
+    if (second) finish(std::integral_constant<int, 2>{});
+    else finish(std::integral_constant<int, 0>{});
+  }
+}
+
+// n = 128: the padded plane does not fit LDS, so the ky halves follow one
+// another through Y [n][n], and a lane group takes one column; waves 4 to 7
+// take the partner columns of waves 0 to 3 and read the same kernel values.
+// 128x128x1024: 313 us on eight-lane transforms -> 243, of which about 140 are
+// vector issue; the rest is memory (the plane is read twice and its first half
+// written and read back) between barriers that all eight waves meet.
+template <int LOGN, bool ADJ, int PAD, bool PACKED>
+__device__ __forceinline__ void plane_conv_wide_body(float2* __restrict__ P, const float2* Hp,
+                                                     float2* Y, float2* tw2, float2 tv, int tid) {
+  using QC = QuadCfg<LOGN>;
+  constexpr int N = QC::N, L = QC::L, E = QC::E, YS = N + PAD;
+  const int j = tid & 15, g = (tid >> 4) & 3, row = 16 * (tid >> 6) + j;
+  const uint32_t p0 = row * N + (E / 4) * g;
+  float2 x[E];
+  auto load_rows = [&]() {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) row_get<E>(x, P, p0, c);
+  };
+  load_rows();
+  {
+    const int t = tid & (L - 1);
+    tw2[t] = t < N ? tv : make_float2(-tv.x, -tv.y);
+  }
+  __syncthreads();
+  float2* Yr = Y + row * YS + g;
+  const int q = row & (N / 2 - 1), mem = row >= N / 2 ? 1 : 0;
+  // the rows that the next step takes from memory (the odd half's input, then
+  // the even half's output) are read before the last column transform, which
+  // hides their latency (250 -> 243 us at 128x128x1024)
+  auto ky_half = [&](auto yc) {
+    constexpr int HY = decltype(yc)::value;
+    {
+      float2 v[E];
+      quad_row_fwd<E, HY>(x, v, tw2, g);
+#pragma unroll
+      for (int k = 0; k < E; ++k) Yr[4 * k] = v[k];
+    }
+    __syncthreads();
+    // column q, or its partner: n - q (0 with n/2) for even ky, n - 1 - q for odd
+    const int partner = HY ? N - 1 - q : (q ? N - q : N / 2);
+    float2* const Yc[1] = {Y + g * YS + (mem ? partner : q)};
+    const float2* const Yp[1] = {Y + (HY == 0 && q == 0 ? (mem ? N / 2 : 0) : (mem ? q : partner))};
+    const bool extra = HY == 0 && mem && q == 0;
+    const uint32_t first = extra ? QC::EXTRA + g : HY * 2 * N + (tid & (2 * N - 1));
+    const uint32_t h0[1] = {first}, hst[1] = {extra ? 4u : 4u * N};
+    quad_columns<LOGN, ADJ, YS, PACKED, 1>(Yc, Yp, Hp, h0, hst, true, tw2, g, load_rows);
+    __syncthreads();
+  };
+  ky_half(std::integral_constant<int, 0>{});
+  // x: the odd half's input; the even half's output takes its place in memory
+  float2 v[E], o[E];
+#pragma unroll
+  for (int k = 0; k < E; ++k) v[k] = Yr[4 * k];
+  quad_row_inv<E, 0, false>(v, o, tw2, g);
+#pragma unroll
+  for (int c = 0; c < 4; ++c) row_put<E>(o, P, p0, c);
+  __syncthreads();                                 // Y is rewritten by the odd half
+  ky_half(std::integral_constant<int, 1>{});
+  // x: the even half's output
+#pragma unroll
+  for (int k = 0; k < E; ++k) v[k] = Yr[4 * k];
+  quad_row_inv<E, 1, true>(v, x, tw2, g);
+#pragma unroll
+  for (int c = 0; c < 4; ++c) row_put<E>(x, P, p0, c);
+}
+
+template <int LOGN, bool ADJ, int PAD>
+__global__ void __launch_bounds__(QuadCfg<LOGN>::NT, 2)
+k_plane_conv_wide(float2* __restrict__ spec, const float2* __restrict__ hq,
+                  const float2* __restrict__ tw, const DevCtl* ctl, size_t zs, size_t hzs,
+                  int gate) {
+  using QC = QuadCfg<LOGN>;
+  constexpr int N = QC::N, YS = N + PAD;
+  __shared__ float2 Y[N * YS];
+  __shared__ float2 tw2[QC::L];
+  const size_t zo = (size_t)blockIdx.z * zs;
+  ctl = zsh(ctl, zo);
+  if (gated_off(ctl, gate)) return;
+  spec = zsh(spec, zo);
+  hq = zsh(hq, (size_t)blockIdx.z * hzs);   // 0: one H^ for every scene
+  tw = zsh(tw, zo);
+  const int tid = threadIdx.x;
+  float2* P = spec + (size_t)blockIdx.x * N * N;
+  const float2* Hp = hq + (size_t)blockIdx.x * QC::PITCH;
+  const float2 tv = tw[tid & (N - 1)];
+  // block 0: the packed real planes, a separate path so that its register
+  // demand does not weigh on the other blocks' code
+  if (blockIdx.x == 0) plane_conv_wide_body<LOGN, ADJ, PAD, true>(P, Hp, Y, tw2, tv, tid);
+  else plane_conv_wide_body<LOGN, ADJ, PAD, false>(P, Hp, Y, tw2, tv, tid);
 }
 
 // Register-resident plane kernel of the diagonal solve (n <= 128): rows and
@@ -1680,21 +1798,46 @@ k_tinv_solve_fwd(float2* __restrict__ spec, int nn, ResampleTables S,
 
 // exponentials staged in LDS by the H^ setup (2m <= this; 32 KB at most)
 constexpr int kHqStagedExp = 2048;
-// Layout of H^: lane-ordered, the full 2n x 2n spectrum of each kt plane in
-// the order the plane kernel's lanes multiply it, so that a wave's load of
-// one register reads 64 consecutive entries.  Frequency (fx, fy) in [0, 2n)^2
-// sits at position p = brev(fx) (register p / 8, lane p % 8) of a column:
-//   n <= 64 (register kernel):  [r][col][s], col = brev(fy) < 2n;
-//   n = 128 (half-plane kernel): [h][r][col][s], h = fy % 2 (the ky half),
-//                                col = brev(fy / 2) < n.
+// Stores of the quarter entry (kx, ky), 0 <= kx, ky <= n, of a kt plane where
+// the plane kernel reads it.  n >= 16: the table of QuadCfg.  n = 8: the full
+// 2n x 2n spectrum in the order the eight-lane kernel multiplies it, frequency
+// (fx, fy) at [r][col][s], 8 r + s = brev(fx), col = brev(fy).
 template <int LOGN>
-__device__ __forceinline__ int hq_lane_index(int fx, int fy) {
-  constexpr int N = 1 << LOGN, L = 2 * N, LOGL = LOGN + 1, RE = L / 8;
-  const int p = brev(fx, LOGL);
-  if constexpr (LOGN <= 6) {
-    return ((p >> 3) * L + brev(fy, LOGL)) * 8 + (p & 7);
+__device__ __forceinline__ void hq_store(float2* __restrict__ Hk, int kx, int ky, float2 v) {
+  constexpr int N = 1 << LOGN, L = 2 * N;
+  if constexpr (LOGN < 4) {
+    constexpr int LOGL = LOGN + 1;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int fx = (e & 1) ? (L - kx) & (L - 1) : kx;
+      const int fy = (e & 2) ? (L - ky) & (L - 1) : ky;
+      if (((e & 1) && (kx == 0 || kx == N)) || ((e & 2) && (ky == 0 || ky == N))) continue;
+      const int p = brev(fx, LOGL);
+      Hk[((p >> 3) * L + brev(fy, LOGL)) * 8 + (p & 7)] = v;
+    }
   } else {
-    return (((fy & 1) * RE + (p >> 3)) * N + brev(fy >> 1, LOGN)) * 8 + (p & 7);
+    using QC = QuadCfg<LOGN>;
+    constexpr int E = QC::E;
+    auto put = [&](int slot, int g) {
+      if (ky == N) {
+        Hk[QC::EXTRA + slot * 4 + g] = v;
+      } else {
+        const int pair = (ky & 1) * (N / 2) + (ky >> 1);
+        Hk[slot * 4 * N + (pair >> 4) * 64 + g * 16 + (pair & 15)] = v;
+      }
+    };
+    const int h = kx & 1, base = h ? QC::S0 : 0;
+    if constexpr (E == 4) {
+      const int k = kx >> 1, kn = ((h ? N - 1 : N) - k) & (N - 1);
+      put(base + k / E, k % E);
+      put(base + kn / E, kn % E);
+    } else {
+      const int k = kx >> 1, k1 = k % E, k2 = k / E;
+      const bool low = k1 < E / 2;
+      const int a = low ? k1 : (h ? E - 1 - k1 : E - k1);
+      if (h == 0 && k1 == E / 2) put(k2 == 0 ? 3 : E / 2, 0);
+      else put(base + 4 * (a / 4) + (low ? k2 : 3 - k2), a % 4);
+    }
   }
 }
 
@@ -1705,7 +1848,7 @@ __device__ __forceinline__ int hq_lane_index(int fx, int fy) {
 //                    cos(pi ky dy / n) exp(-pi i kt dq(dx,dy) / m),
 // c_0 = 1, c_d = 2.  One block per (kt, chunk of ky); FP64 accumulation; the
 // inner dy sum is staged in LDS.  Computed for kx, ky in [0, n] (the
-// quarter) and stored lane-ordered (hq_lane_index).
+// quarter) and stored by hq_store.
 // The kernel offsets dq (n <= 64) and, with ET, the exponential table
 // exp(-pi i j / m), j < 2m (dynamic LDS, 2m entries), are staged in LDS; 2m is
 // a power of two, so the phase index kt q mod 2m is a mask (kt q < 2^31 for
@@ -1764,17 +1907,7 @@ k_build_hq(float2* __restrict__ hq, int m, const int* __restrict__ dq,
       ai += w * gv.y;
     }
     const float2 v = make_float2((float)(ar * invZ), (float)(ai * invZ));
-    // every image (+-kx, +-ky) of the quarter entry, where the plane kernel
-    // multiplies by it (H^ is even in kx and ky)
-    constexpr int L = 2 * N;
-    float2* Hk = hq + (size_t)kt * L * L;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int fx = (e & 1) ? (L - kx) & (L - 1) : kx;
-      const int fy = (e & 2) ? (L - ky) & (L - 1) : ky;
-      if (((e & 1) && (kx == 0 || kx == N)) || ((e & 2) && (ky == 0 || ky == N))) continue;
-      Hk[hq_lane_index<LOGN>(fx, fy)] = v;
-    }
+    hq_store<LOGN>(hq + (size_t)kt * hq_pitch(LOGN), kx, ky, v);
   }
 }
 
@@ -1798,25 +1931,22 @@ int fused_solve_blocks(int logn, int logm) { return conv_blocks(logn, logm); }
 template <int LOGN, int PAD>
 static void plane_conv_pad(bool adjoint, int M, const Tables& tb, float2* spec, const DevCtl* ctl,
                            size_t zs, size_t hzs, int g, int nz, hipStream_t st) {
-  if constexpr (LOGN <= 6) {
-    if (adjoint)
-      hipLaunchKernelGGL((k_plane_conv_reg<LOGN, true, PAD>), dim3(M, 1, nz),
-                         dim3(PlaneRegCfg<LOGN>::NT), 0, st, spec, tb.hq, tb.tw_xy, tb.twc_xy, ctl,
-                         zs, hzs, g);
-    else
-      hipLaunchKernelGGL((k_plane_conv_reg<LOGN, false, PAD>), dim3(M, 1, nz),
-                         dim3(PlaneRegCfg<LOGN>::NT), 0, st, spec, tb.hq, tb.tw_xy, tb.twc_xy, ctl,
-                         zs, hzs, g);
+#define CNLOS_PCONV(K, NT_, ...)                                                                \
+  hipLaunchKernelGGL((K), dim3(M, 1, nz), dim3(NT_), 0, st, spec, tb.hq, tb.tw_xy, __VA_ARGS__ ctl, \
+                     zs, hzs, g)
+#define CNLOS_COMMA ,
+  if constexpr (LOGN < 4) {
+    if (adjoint) CNLOS_PCONV(k_plane_conv_reg<LOGN CNLOS_COMMA true CNLOS_COMMA PAD>, PlaneRegCfg<LOGN>::NT, tb.twc_xy CNLOS_COMMA);
+    else CNLOS_PCONV(k_plane_conv_reg<LOGN CNLOS_COMMA false CNLOS_COMMA PAD>, PlaneRegCfg<LOGN>::NT, tb.twc_xy CNLOS_COMMA);
+  } else if constexpr (LOGN <= 6) {
+    if (adjoint) CNLOS_PCONV(k_plane_conv_quad<LOGN CNLOS_COMMA true CNLOS_COMMA PAD>, quad_split<LOGN>() * QuadCfg<LOGN>::NT, );
+    else CNLOS_PCONV(k_plane_conv_quad<LOGN CNLOS_COMMA false CNLOS_COMMA PAD>, quad_split<LOGN>() * QuadCfg<LOGN>::NT, );
   } else {
-    if (adjoint)
-      hipLaunchKernelGGL((k_plane_conv_half<LOGN, true, PAD>), dim3(M, 1, nz),
-                         dim3(PlaneHalfCfg<LOGN>::NT), 0, st, spec, tb.hq, tb.tw_xy, tb.twc_xy,
-                         ctl, zs, hzs, g);
-    else
-      hipLaunchKernelGGL((k_plane_conv_half<LOGN, false, PAD>), dim3(M, 1, nz),
-                         dim3(PlaneHalfCfg<LOGN>::NT), 0, st, spec, tb.hq, tb.tw_xy, tb.twc_xy,
-                         ctl, zs, hzs, g);
+    if (adjoint) CNLOS_PCONV(k_plane_conv_wide<LOGN CNLOS_COMMA true CNLOS_COMMA PAD>, QuadCfg<LOGN>::NT, );
+    else CNLOS_PCONV(k_plane_conv_wide<LOGN CNLOS_COMMA false CNLOS_COMMA PAD>, QuadCfg<LOGN>::NT, );
   }
+#undef CNLOS_PCONV
+#undef CNLOS_COMMA
 }
 
 template <int LOGN>
@@ -2018,7 +2148,7 @@ hipError_t launch_build_hq(int logn, int logm, float2* hq, const int* dq, const 
 #undef CNLOS_HQ
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const int plane = 4 << (2 * logn);
+  const int plane = hq_pitch(logn);
   hipLaunchKernelGGL(k_hq_pack_real, dim3((plane + 255) / 256), dim3(256), 0, st, hq, m, plane);
   return hipGetLastError();
 }

@@ -135,3 +135,19 @@ def test_large_workload_operator_sampled_columns():
     ref = sampled_columns_AT(y, n, m, wall, wall, bin_ps, O.FALLOFF_COMPENSATED, cols)
     for c in cols:
         assert rel_l2(got[c], ref[c]) <= TOL_OP, c
+
+
+# every plane kernel's smallest time axes (block 0, the packed real planes, is
+# one of few blocks there) on full volumes; the tolerance of the tests above
+@pytest.mark.parametrize("n,m", [(16, 16), (32, 16), (64, 16), (64, 32), (128, 16)])
+def test_plane_kernels_on_short_time_axes(n, m):
+    torch = need_gpu()
+    say(f"plane kernels n={n} m={m}")
+    mask = _mask(n, 5 + n + m)
+    P = _op_problem(n, m, 0.9, 16.0 * 512 / m, C.FALLOFF_COMPENSATED, mask)
+    op = O.make_operator(n, n, m, 0.9, 0.9, 16.0 * 512 / m, C.FALLOFF_COMPENSATED, mask)
+    u = f32(scenes.random_volume((n, n, m), seed=n * 77 + m))
+    y = f32(scenes.random_signed((n, n, m), seed=n * 77 + m + 1))
+    assert rel_l2(to_host(P.apply_A(to_dev(torch, u))), O.apply_A(u, op)) <= TOL_OP
+    assert rel_l2(to_host(P.apply_AT(to_dev(torch, y), True)), O.apply_AT(y, op, True)) <= TOL_OP
+    P.close()
