@@ -16,19 +16,27 @@ namespace cnlos {
 constexpr int kStencilThreads = 256;
 constexpr int kCtlThreads = 1024;
 
-// Blocks of the stencil kernels: one thread per voxel (bin pair) up to a cap
-// that the volume sets.  Each block walks a contiguous range of bin pairs, and
-// all blocks of an XCD read the neighbour rows of each other's ranges at
-// about the same time, so how many run at once decides whether those reads
-// still find the data in L2.  Measured for the post kernels: 2048 blocks at
-// 2^21 voxels (64x64x512: 42.4 against 45.4 us per launch with 1024), 512 at
-// 2^24 (128x128x1024: 442 against 463 us); 1024 between.  The count is fixed
-// by the shape, so results do not depend on timing.
+// Blocks of the stencil kernels: two bin pairs per thread, up to a cap that the
+// volume sets.  A block of the post kernels costs its share of the backtracking
+// decision (the check and step partials) and an FP64 block sum whatever it
+// works on, so one pair per thread, and blocks without any, lose more than the
+// waves they add: per iteration of the dual model (with every block busy and
+// two pairs per thread, against up to one voxel per thread, half of the blocks
+// idle) eight scenes of 32x32x256 together 235 -> 193 us, one 88.6 -> 79.9
+// (these figures include the plane kernels' change from eight to four lanes).
+// Each block walks a contiguous range of bin pairs, and all blocks of an XCD
+// read the neighbour rows of each other's ranges at about the same time, so how
+// many run at once decides whether those reads still find the data in L2.
+// Measured for the post kernels: 2048 blocks at 2^21 voxels (64x64x512: 42.4
+// against 45.4 us per launch with 1024), 512 at 2^24 (128x128x1024: 442 against
+// 463 us); 1024 between.  The count is fixed by the shape, so results do not
+// depend on timing or on the batch.
 int stencil_blocks(int logn, int logm) {
   const int logv = 2 * logn + logm;
   const size_t V = (size_t)1 << logv;
   const size_t cap = logv <= 21 ? 2048 : (logv >= 24 ? 512 : 1024);
-  size_t nb = (V + kStencilThreads - 1) / kStencilThreads;
+  const size_t per = 4 * kStencilThreads;
+  size_t nb = (V + per - 1) / per;
   if (nb > cap) nb = cap;
   return (int)nb;
 }
