@@ -214,10 +214,10 @@ struct cnlos_problem {
   float2* tw_xy = nullptr;
   float2* twc_t = nullptr;
   float2* twc_xy = nullptr;
-  int4* srows = nullptr;
-  float* srvals = nullptr;
-  int4* scols = nullptr;
-  float* scvals = nullptr;
+  float4* srows = nullptr;
+  float2* fa = nullptr;
+  float4* scols = nullptr;
+  float2* fb = nullptr;
   float* wk = nullptr;
   float* r3 = nullptr;
   float* sig_xy = nullptr;
@@ -296,10 +296,9 @@ void Prof::release() {
 
 namespace {
 
-int resample_nnz(int m) {
-  // counted exactly when the tables are built; this bound sizes the buffer
-  return 3 * m + 64;
-}
+// floats held for each table of the column transforms' lane twiddles (checked
+// when they are built)
+int column_tw_floats(int m) { return 3 * m + 64; }
 
 // bytes that a workspace holds for one H^: 4 n^2 entries per kt plane, the most
 // that a plane kernel's table takes (hq_pitch; the full spectrum at n = 8)
@@ -326,10 +325,10 @@ size_t carve(cnlos_problem* p, const cnlos_config& c, uint8_t* base, bool own_hq
   float2* tw_xy = cv.take<float2>(n);
   float2* twc_t = cv.take<float2>(m);
   float2* twc_xy = cv.take<float2>(2 * n);
-  int4* srows = cv.take<int4>(m);
-  float* srvals = cv.take<float>(resample_nnz(m));
-  int4* scols = cv.take<int4>(m);
-  float* scvals = cv.take<float>(resample_nnz(m));
+  float4* srows = cv.take<float4>(m);
+  float2* fa = reinterpret_cast<float2*>(cv.take<float>(column_tw_floats(m)));
+  float4* scols = cv.take<float4>(m);
+  float2* fb = reinterpret_cast<float2*>(cv.take<float>(column_tw_floats(m)));
   float* wk = cv.take<float>(m);
   float* r3 = cv.take<float>(m);
   float* sig_xy = cv.take<float>(n);
@@ -346,9 +345,9 @@ size_t carve(cnlos_problem* p, const cnlos_config& c, uint8_t* base, bool own_hq
     p->twc_t = twc_t;
     p->twc_xy = twc_xy;
     p->srows = srows;
-    p->srvals = srvals;
+    p->fa = fa;
     p->scols = scols;
-    p->scvals = scvals;
+    p->fb = fb;
     p->wk = wk;
     p->r3 = r3;
     p->sig_xy = sig_xy;
@@ -1156,36 +1155,53 @@ cnlos_status build_tables(cnlos_problem* p, const cnlos_config* cfg, const uint8
       }
     }
   }
-  std::vector<int4> srows(m), scols(m);
-  std::vector<float> srv, scv;
-  // the t pass computes rows of more than 3 taps from prefix sums of the first
-  // resample_scan_rows lane-rows of the column and takes their interior
-  // weights as 1: check both
+  // One descriptor per row and column.  At most 3 taps: the weights of three
+  // neighbouring samples from a base on (clamped so that all three exist).
+  // Longer R_z rows: the t pass computes them from prefix sums of the first
+  // resample_scan_rows lane-rows of the column, takes their interior weights as
+  // 1, and expects them below resample_long_rows: check all three.
+  auto bits = [](int x) {
+    float f;
+    memcpy(&f, &x, sizeof(f));
+    return f;
+  };
+  auto describe = [&](const std::vector<std::pair<int, double>>& v) {
+    const int base = v.empty() ? 0 : std::min(v[0].first, m - 3);
+    float w[3] = {0.f, 0.f, 0.f};
+    for (const auto& t : v) w[t.first - base] = (float)t.second;
+    return make_float4(w[0], w[1], w[2], bits(base | (base + 2) << 12));
+  };
+  std::vector<float4> srows(m), scols(m);
   const int lanes = m / 2 < 64 ? m / 2 : 64;
   const int scan_end = resample_scan_rows(m, lanes) * lanes;
   for (int q = 0; q < m; ++q) {
-    if (rows[q].size() > 3) {
-      if (rows[q].back().first + 1 > scan_end)
-        return fail(CNLOS_EINVAL, "long resampling row beyond the prefix-summed range");
-      for (size_t t = 1; t + 1 < rows[q].size(); ++t)
-        if ((float)rows[q][t].second != 1.f) return fail(CNLOS_EINVAL, "resampling interior weight is not 1");
+    const auto& v = rows[q];
+    for (size_t t = 0; t < v.size(); ++t)
+      if (v[t].first != v[0].first + (int)t) return fail(CNLOS_EINVAL, "resampling row not contiguous");
+    if (v.size() <= 3) {
+      srows[q] = describe(v);
+      continue;
     }
-    srows[q] = make_int4(rows[q].empty() ? 0 : rows[q][0].first, (int)rows[q].size(), (int)srv.size(), 0);
-    for (size_t t = 0; t < rows[q].size(); ++t) {
-      if (rows[q][t].first != rows[q][0].first + (int)t) return fail(CNLOS_EINVAL, "resampling row not contiguous");
-      srv.push_back((float)rows[q][t].second);
-    }
+    const int k0 = v[0].first, k2 = v.back().first;
+    if (k2 + 1 > scan_end || q >= resample_long_rows(m))
+      return fail(CNLOS_EINVAL, "long resampling row beyond the prefix-summed range");
+    for (size_t t = 1; t + 1 < v.size(); ++t)
+      if ((float)v[t].second != 1.f) return fail(CNLOS_EINVAL, "resampling interior weight is not 1");
+    srows[q] = make_float4((float)v[0].second, 0.f, (float)v.back().second,
+                           bits(k0 | k2 << 12 | 1 << 24));
   }
   for (int k = 0; k < m; ++k) {
-    if (cols[k].size() > 3) return fail(CNLOS_EINVAL, "resampling column of more than 3 taps");
-    scols[k] = make_int4(cols[k].empty() ? 0 : cols[k][0].first, (int)cols[k].size(), (int)scv.size(), 0);
-    for (size_t t = 0; t < cols[k].size(); ++t) {
-      if (cols[k][t].first != cols[k][0].first + (int)t) return fail(CNLOS_EINVAL, "resampling column not contiguous");
-      scv.push_back((float)cols[k][t].second);
-    }
+    const auto& v = cols[k];
+    if (v.size() > 3) return fail(CNLOS_EINVAL, "resampling column of more than 3 taps");
+    for (size_t t = 0; t < v.size(); ++t)
+      if (v[t].first != v[0].first + (int)t) return fail(CNLOS_EINVAL, "resampling column not contiguous");
+    scols[k] = describe(v);
+    scols[k].w = bits(v.empty() ? 0 : std::min(v[0].first, m - 3));
   }
-  if ((int)srv.size() > resample_nnz(m) || (int)scv.size() > resample_nnz(m))
-    return fail(CNLOS_EINVAL, "resampling table larger than its bound");
+  std::vector<float2> fa, fb;
+  column_twiddles(p->logm, fa, fb);
+  if ((int)std::max(fa.size(), fb.size()) * 2 > column_tw_floats(m))
+    return fail(CNLOS_EINVAL, "twiddle table larger than its bound");
   std::vector<float> wk(m), r3(m), sig_xy(n), sig_t(m / 2 + 1);
   for (int k = 0; k < m; ++k) {
     const double r = (k + 0.5) / m;
@@ -1234,10 +1250,10 @@ cnlos_status build_tables(cnlos_problem* p, const cnlos_config* cfg, const uint8
   HIPCHK(h2d(p->tw_xy, tw_xy.data(), n * sizeof(float2)));
   HIPCHK(h2d(p->twc_t, twc_t.data(), m * sizeof(float2)));
   HIPCHK(h2d(p->twc_xy, twc_xy.data(), 2 * n * sizeof(float2)));
-  HIPCHK(h2d(p->srows, srows.data(), m * sizeof(int4)));
-  HIPCHK(h2d(p->scols, scols.data(), m * sizeof(int4)));
-  HIPCHK(h2d(p->srvals, srv.data(), srv.size() * sizeof(float)));
-  HIPCHK(h2d(p->scvals, scv.data(), scv.size() * sizeof(float)));
+  HIPCHK(h2d(p->srows, srows.data(), m * sizeof(float4)));
+  HIPCHK(h2d(p->scols, scols.data(), m * sizeof(float4)));
+  if (!fa.empty()) HIPCHK(h2d(p->fa, fa.data(), fa.size() * sizeof(float2)));
+  if (!fb.empty()) HIPCHK(h2d(p->fb, fb.data(), fb.size() * sizeof(float2)));
   HIPCHK(h2d(p->wk, wk.data(), m * sizeof(float)));
   HIPCHK(h2d(p->r3, r3.data(), m * sizeof(float)));
   HIPCHK(h2d(p->sig_xy, sig_xy.data(), n * sizeof(float)));
@@ -1254,10 +1270,10 @@ cnlos_status build_tables(cnlos_problem* p, const cnlos_config* cfg, const uint8
   p->tb.tw_xy = p->tw_xy;
   p->tb.twc_t = p->twc_t;
   p->tb.twc_xy = p->twc_xy;
+  p->tb.fa = p->fa;
+  p->tb.fb = p->fb;
   p->tb.S.rows = p->srows;
-  p->tb.S.rvals = p->srvals;
   p->tb.S.cols = p->scols;
-  p->tb.S.cvals = p->scvals;
   p->tb.sig_xy = p->sig_xy;
   p->tb.sig_t = p->sig_t;
   p->tb.hq = p->hq;

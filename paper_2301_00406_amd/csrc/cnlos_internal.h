@@ -209,12 +209,10 @@ __device__ __forceinline__ float* vol_resolve(const Vol& v, const CtlHead& h, si
 }
 
 // Sparse resampling table S (depth bin k -> squared-distance bin q) in both
-// orientations; ranges are contiguous so each row/column is (start, count, off).
+// orientations, one 16-byte descriptor per row or column (rz_row, st_taps).
 struct ResampleTables {
-  const int4* rows;    // [m]: (k_start, count, value_offset, 0)
-  const float* rvals;
-  const int4* cols;    // [m]: (q_start, count, value_offset, 0)
-  const float* cvals;
+  const float4* rows;    // [m]: R_z rows, (w, w', w'', k0 | k2 << 12 | long << 24)
+  const float4* cols;    // [m]: columns of at most 3 taps, (w, w', w'', q0)
 };
 
 // Source of the t-axis forward pass of a convolution:
@@ -287,6 +285,8 @@ struct Tables {
   const float2* tw_xy;    // exp(-2 pi i j / (2n)), j < n
   const float2* twc_t;    // per-span butterfly twiddles: [d + k] = exp(-pi i k / d), size m
   const float2* twc_xy;   // the same for the (x, y) transforms, size 2n
+  const float2* fa;       // lane twiddles of the column transforms' passes
+  const float2* fb;       // (column_twiddles)
   ResampleTables S;
   const float* sig_xy;    // 4 sin^2(pi k / n), k < n
   const float* sig_t;     // 4 sin^2(pi k / m), k <= m/2
@@ -306,6 +306,10 @@ constexpr int resample_scan_rows(int M, int G) {
   const int r = (M / 4 + 8 + G - 1) / G;
   return r < M / G ? r : M / G;
 }
+
+// R_z rows of more than 3 taps lie below this bin (the table builder checks it).
+constexpr int resample_long_rows(int M) { return M / 8; }
+void column_twiddles(int logm, std::vector<float2>& fa, std::vector<float2>& fb);
 
 // XCD-aware block order.  Workgroups are dealt round-robin over the 8 XCDs,
 // each with its own L2; logical block xcd_block(b, nb) places nb / 8

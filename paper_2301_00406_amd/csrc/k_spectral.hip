@@ -15,9 +15,12 @@
 // columns are transformed with their zero halves folded into twists, and the
 // n x n crop is taken before anything leaves the CU (n = 128 takes the ky
 // parities one after the other to fit LDS).
+#include <math.h>
+
 #include "cnlos_internal.h"
 #include "fft_device.h"
 #include "fft_quad.h"
+#include "fft_column.h"
 #include "stencil_device.h"
 
 namespace cnlos {
@@ -29,13 +32,6 @@ __device__ __forceinline__ const float* vol_in(const Vol& v, const CtlHead& h, s
 __device__ __forceinline__ float* vol_out(const Vol& v, const CtlHead& h, size_t zo) {
   return vol_resolve(v, h, zo);
 }
-__device__ __forceinline__ void zsh_tables(ResampleTables& S, size_t zo) {
-  S.rows = zsh(S.rows, zo);
-  S.rvals = zsh(S.rvals, zo);
-  S.cols = zsh(S.cols, zo);
-  S.cvals = zsh(S.cvals, zo);
-}
-
 // ---------------------------------------------------------------------------
 // t passes.  A block handles J scan columns (t_columns); each column's FFT
 // lives in the registers of a group of G <= 64 lanes, so within one wave
@@ -54,6 +50,10 @@ __device__ __forceinline__ void zsh_tables(ResampleTables& S, size_t zo) {
 // transforms (the solve phase of a fused pass needs whole waves), 4 at 2048
 // (LDS).
 constexpr int t_columns(int logf) { return logf <= 7 ? 16 : (logf <= 10 ? 8 : 4); }
+
+// waves per SIMD that a t pass is compiled for: two blocks of 512 threads per CU
+// at length 1024 (their LDS allows it; the epilogues' registers need the cap)
+constexpr int t_waves(int logf) { return logf == 10 ? 4 : 1; }
 
 template <int LOGF>
 struct TGeo {                                 // transform of length F = 2^LOGF
@@ -131,91 +131,228 @@ __device__ __forceinline__ auto table_copy(T* dst, const T* __restrict__ src) {
   return split_copy<NT, COUNT>([=](int i) { return src[i]; }, [=](int i, T v) { dst[i] = v; });
 }
 
-// LDS index of staging element (kt, column b): rows of J + 1 plus one extra
-// slot every 8 rows, so that rows kt and kt + 8 (bit-reversed neighbours) and
-// consecutive rows fall into different banks.
 template <int J>
-__device__ __forceinline__ int stg(int k, int b) { return k * (J + 1) + (k >> 3) + b; }
-template <int J>
-constexpr int stg_size(int rows) { return rows * (J + 1) + rows / 8 + J; }
-// planes k < NP of the block's J columns <-> the LDS staging tile
-template <int J, int NT, int NP>
-__device__ __forceinline__ auto planes_copy(float2* lds, const float2* __restrict__ spec, int nn,
-                                            int col0) {
-  return split_copy<NT, NP * J>(
-      [=](int it) { return spec[(size_t)(it / J) * nn + col0 + it % J]; },
-      [=](int it, float2 v) { lds[stg<J>(it / J, it % J)] = v; });
-}
-template <int J, int NT, int NP>
-__device__ __forceinline__ void lds_to_planes(const float2* lds, float2* __restrict__ spec, int nn,
-                                              int col0, int tid) {
-  block_copy<NT, NP * J>(
-      tid, [&](int it) { return lds[stg<J>(it / J, it % J)]; },
-      [&](int it, float2 v) { spec[(size_t)(it / J) * nn + col0 + it % J] = v; });
-}
-// LDS index of a column's transform element p, padded every 8 elements so
-// that bit-reversed access patterns spread over the banks.
-__device__ __forceinline__ int zix(int p) { return p + (p >> 3); }
-
-// The resampling sums below are branch-free: a load under a per-lane
-// condition compiles to a branch with a wait after it, so the indices of
-// absent taps are clamped into the row (or to 0 for an empty row) and their
-// terms masked by selects; all of a lane's table and sample loads can then
-// issue together.  The sums keep the order of the tap-by-tap form.
+constexpr int stg_size(int rows) { return rows * (J + 1) + rows / 8 + J; }   // see z_at
+// The real transforms' (un)tangling.  A real column of 2F samples is one
+// complex transform Z of length F of its pairs; its spectrum X[0 .. F] and Z
+// are related per pair of frequencies (k, F - k), so the thread that moves
+// such a pair between the planes and the LDS staging tile does both at once (one
+// complex product for two frequencies, and the tile holds Z in natural order).
+// Planes: kt = 0 .. F - 1, plane 0 holding X_0 + i X_F (both real).  The pair
+// of k = 0 is k = F/2, whose twiddle is -i: Z = conj(X) there.
+// W^k = exp(-pi i k / F) = tw[STEP k].
 //
-// R_z of one z bin from its row (first sample k0, cnt taps, weights at off):
-// rows of more than 3 taps (interior weights exactly 1) from the exclusive
-// prefix sums pf, shorter rows tap by tap.
-__device__ __forceinline__ float rz_row(const int4 ri, const float* sval, const float* xf,
-                                        const float* pf) {
-  const int cnt = ri.y;
-  const bool any = cnt > 0;
-  const int k0 = any ? ri.x : 0, off = any ? ri.z : 0;
-  const int t1 = any ? cnt - 1 : 0, i1 = cnt > 1 ? 1 : 0;
-  const float wa = sval[off], wb = sval[off + t1], wm = sval[off + i1];
-  const float xa = xf[k0], xb = xf[k0 + t1], xm = xf[k0 + i1];
-  const float pa = pf[k0 + t1], pb = pf[k0 + i1];
-  const float acc_l = wa * xa + (pa - pb) + wb * xb;
-  float acc_s = wa * xa;
-  acc_s = cnt == 3 ? fmaf(wm, xm, acc_s) : acc_s;
-  acc_s = cnt >= 2 ? fmaf(wb, xb, acc_s) : acc_s;
-  return cnt > 3 ? acc_l : (any ? acc_s : 0.f);
+// planes -> Z: loads and stores split as in SplitCopy
+template <int J, int NT, int LOGF, int STEP>
+struct TangleCopy {
+  static constexpr int F = 1 << LOGF, COUNT = F / 2 * J, NS = (COUNT + NT - 1) / NT;
+  float2* lds;
+  const float2* __restrict__ spec;
+  const float2* __restrict__ tw;
+  int nn, col0;
+  float2 a[NS], b[NS], w[NS];
+  __device__ __forceinline__ static int at(int tid, int j) {
+    const int it = tid + j * NT;
+    return it < COUNT ? it : COUNT - 1;
+  }
+  __device__ __forceinline__ void load(int tid) {
+#pragma unroll
+    for (int j = 0; j < NS; ++j) {
+      const int it = at(tid, j), k = it / J, c = col0 + it % J, kp = k ? F - k : F / 2;
+      a[j] = spec[(size_t)k * nn + c];
+      b[j] = spec[(size_t)kp * nn + c];
+      w[j] = tw[STEP * k];
+    }
+  }
+  __device__ __forceinline__ void store(int tid) {
+#pragma unroll
+    for (int j = 0; j < NS; ++j) {
+      const int it = at(tid, j), k = it / J, c = it % J, kp = k ? F - k : F / 2;
+      const float2 e = make_float2(0.5f * (a[j].x + b[j].x), 0.5f * (a[j].y - b[j].y));
+      const float2 o = make_float2(0.5f * (a[j].x - b[j].x), 0.5f * (a[j].y + b[j].y));
+      const float2 q = cmulc(o, w[j]);
+      const bool z = k == 0;
+      const float2 zk = make_float2(z ? 0.5f * (a[j].x + a[j].y) : e.x - q.y,
+                                    z ? 0.5f * (a[j].x - a[j].y) : e.y + q.x);
+      const float2 zp = make_float2(z ? b[j].x : e.x + q.y, z ? -b[j].y : q.x - e.y);
+      lds[z_at<LOGF, J>(z_row<LOGF>(k), c)] = zk;
+      lds[z_at<LOGF, J>(z_row<LOGF>(kp), c)] = zp;
+    }
+  }
+};
+template <int J, int NT, int LOGF, int STEP>
+__device__ __forceinline__ auto tangle_copy(float2* lds, const float2* __restrict__ spec,
+                                            const float2* __restrict__ tw, int nn, int col0) {
+  return TangleCopy<J, NT, LOGF, STEP>{lds, spec, tw, nn, col0, {}, {}, {}};
+}
+// Z (staged) -> planes
+template <int J, int NT, int LOGF, int STEP>
+__device__ __forceinline__ void untangle_to_planes(const float2* lds, const float2* __restrict__ tw,
+                                                   float2* __restrict__ spec, int nn, int col0,
+                                                   int tid) {
+  constexpr int F = 1 << LOGF, COUNT = F / 2 * J, NS = (COUNT + NT - 1) / NT;
+#pragma unroll
+  for (int j = 0; j < NS; ++j) {
+    const int it = tid + j * NT;
+    if (NS * NT > COUNT && it >= COUNT) break;
+    const int k = it / J, c = it % J, kp = k ? F - k : F / 2;
+    const float2 zk = lds[z_at<LOGF, J>(z_row<LOGF>(k), c)];
+    const float2 zp = lds[z_at<LOGF, J>(z_row<LOGF>(kp), c)];
+    const float2 e = make_float2(0.5f * (zk.x + zp.x), 0.5f * (zk.y - zp.y));
+    const float2 o = make_float2(0.5f * (zk.x - zp.x), 0.5f * (zk.y + zp.y));
+    const float2 q = cmul(o, tw[STEP * k]);
+    const bool z = k == 0;
+    spec[(size_t)k * nn + col0 + c] =
+        make_float2(z ? zk.x + zk.y : e.x + q.y, z ? zk.x - zk.y : e.y - q.x);
+    spec[(size_t)kp * nn + col0 + c] =
+        make_float2(z ? zp.x : e.x - q.y, z ? -zp.y : -e.y - q.x);
+  }
 }
 
-// S^T of one t bin from its column of at most 3 taps (first sample x, weights
-// at z; checked on the host).
-__device__ __forceinline__ float st_taps(const int4 ci, const float* sval, const float* g) {
-  const int cnt = ci.y;
-  const int x = cnt > 0 ? ci.x : 0, z = cnt > 0 ? ci.z : 0;
-  const int i1 = cnt > 1 ? 1 : 0, i2 = cnt > 2 ? 2 : i1;
-  const float w0 = sval[z], w1 = sval[z + i1], w2 = sval[z + i2];
-  const float g0 = g[x], g1 = g[x + i1], g2 = g[x + i2];
-  float tk = cnt > 0 ? w0 * g0 : 0.f;
-  tk = cnt > 1 ? fmaf(w1, g1, tk) : tk;
-  tk = cnt > 2 ? fmaf(w2, g2, tk) : tk;
-  return tk;
+// A column's spectrum between its lanes' registers and the staging tile.
+// Radix-2 form: position G r + s holds the bit-reversed frequency.
+template <int LOGF, int J>
+__device__ __forceinline__ void stage_put(float2* lds, const float2 (&x)[FftCol<LOGF>::E], int b,
+                                          int s) {
+  using C = FftCol<LOGF>;
+#pragma unroll
+  for (int r = 0; r < C::E; ++r)
+    lds[z_at<LOGF, J>(C::PASS ? 64 * r + s : brev(C::G * r + s, LOGF), b)] = x[r];
 }
+template <int LOGF, int J>
+__device__ __forceinline__ void stage_get(const float2* lds, float2 (&x)[FftCol<LOGF>::E], int b,
+                                          int s) {
+  using C = FftCol<LOGF>;
+#pragma unroll
+  for (int r = 0; r < C::E; ++r)
+    x[r] = lds[z_at<LOGF, J>(C::PASS ? 64 * r + s : brev(C::G * r + s, LOGF), b)];
+}
+// The transforms (tws, twc: the radix-2 form's tables in LDS; slot: the column's
+// LDS).  HALF: zero upper half (the padded input); CROP: lower half only.
+template <int LOGF, bool HALF, int TSTEP>
+__device__ __forceinline__ void col_transform_fwd(float2 (&x)[FftCol<LOGF>::E], float2* slot,
+                                                  const FftTw<LOGF>& tw, const float2* tws,
+                                                  const float2* twc, int s) {
+  using C = FftCol<LOGF>;
+  if constexpr (C::PASS) {
+    passes_fwd<LOGF, HALF>(x, slot, tw, s);
+  } else {
+    if constexpr (HALF) {
+#pragma unroll
+      for (int r = 0; r < C::E / 2; ++r)
+        x[r + C::E / 2] = cmul(x[r], tws[TSTEP * 2 * (C::G * r + s)]);
+    }
+    dif_inlane<C::G, C::E, HALF ? C::E / 4 : C::E / 2>(x, s, twc);
+    dif_xlane<C::G, C::E>(x, s, twc);
+  }
+}
+template <int LOGF, bool CROP, int TSTEP>
+__device__ __forceinline__ void col_transform_inv(float2 (&x)[FftCol<LOGF>::E], float2* slot,
+                                                  const FftTw<LOGF>& tw, const float2* tws,
+                                                  const float2* twc, int s) {
+  using C = FftCol<LOGF>;
+  if constexpr (C::PASS) {
+    passes_inv<LOGF, CROP>(x, slot, tw, s);
+  } else {
+    dit_xlane<C::G, C::E>(x, s, twc);
+    dit_inlane<C::G, C::E, CROP ? C::E / 4 : C::E / 2>(x, s, twc);
+    if constexpr (CROP) {
+#pragma unroll
+      for (int r = 0; r < C::E / 2; ++r)
+        x[r] = cadd(x[r], cmulc(x[r + C::E / 2], tws[TSTEP * 2 * (C::G * r + s)]));
+    }
+  }
+}
+// Twiddle tables of a launch: the radix-2 form's (tw: exp(-pi i j / m); twc per
+// span) and the passes' (fa, fb: the convolution's, then the solve's).
+struct TwTabs {
+  const float2* tw;
+  const float2* twc;
+  const float2* fa;
+  const float2* fb;
+};
+__device__ __forceinline__ void zsh_tw(TwTabs& t, size_t zo) {
+  t.tw = zsh(t.tw, zo);
+  t.twc = zsh(t.twc, zo);
+  t.fa = zsh(t.fa, zo);
+  t.fb = zsh(t.fb, zo);
+}
+
+// The resampling rows and columns as descriptors of one 16-byte read (built on
+// the host): weights of three neighbouring samples from a base on (0 where the
+// row has fewer; the base is clamped so that all three exist), or for an R_z
+// row of more than 3 taps, whose interior weights are exactly 1, the end
+// weights (x, z) with both ends' indices, the interior coming from the prefix
+// sums pf.  Such rows lie below m/8 (resample_long_rows; LONG: the row may be one).
+template <bool LONG, typename PT>
+__device__ __forceinline__ float rz_row(const float4 d, const float* xf, const PT* pf) {
+  const int bits = __float_as_int(d.w), k0 = bits & 0xfff;
+  const float s = fmaf(d.y, xf[k0 + 1], d.x * xf[k0]);
+  if constexpr (!LONG) {
+    return fmaf(d.z, xf[k0 + 2], s);
+  } else {
+    const bool lg = (bits >> 24) != 0;
+    const int k2 = (bits >> 12) & 0xfff;                 // k0 + 2, or the row's end
+    const float in = (float)(pf[k2] - pf[k0 + 1]);
+    return fmaf(d.z, xf[k2], s + (lg ? in : 0.f));
+  }
+}
+__device__ __forceinline__ float st_taps(const float4 d, const float* g) {
+  const int x = __float_as_int(d.w);
+  return fmaf(d.z, g[x + 2], fmaf(d.y, g[x + 1], d.x * g[x]));
+}
+
+// Inclusive prefix sum over the 64 lanes (DPP: within rows of 16 lanes, then
+// across them).  In FP64: an R_z row takes the difference of two prefix sums,
+// and with FP32 sums in this order the dual model's volumes were half as far
+// again from the FP64 result (32x32x256, 16 iterations: 8.6e-7 against 5.8e-7).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_add(double v) {
+  const unsigned long long u = (unsigned long long)__double_as_longlong(v);
+  const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)u, CTRL, ROWS, 0xf, false);
+  const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(u >> 32), CTRL, ROWS, 0xf, false);
+  return v + __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+__device__ __forceinline__ double wave_scan(double v) {
+  v = dpp_add<0x111, 0xf>(v);       // row_shr:1, 2, 4, 8
+  v = dpp_add<0x112, 0xf>(v);
+  v = dpp_add<0x114, 0xf>(v);
+  v = dpp_add<0x118, 0xf>(v);
+  v = dpp_add<0x142, 0xa>(v);       // row_bcast:15 into rows 1 and 3
+  return dpp_add<0x143, 0xc>(v);    // row_bcast:31 into rows 2 and 3
+}
+// type of the prefix sums: FP64 where a column has a whole wave
+template <int LOGM>
+using Prefix = typename std::conditional<TGeo<LOGM>::G == 64, double, float>::type;
 
 // t pass, forward, convolution: x -> R_z x -> zero-pad to 2m -> R2C -> planes.
 // The real length-2m transform is a complex length-m transform of the packed
 // pairs (x[2p], x[2p+1]); its upper half is zero, so the first DIF stage is a
-// twist.  With PK the two real bins kt = 0 and kt = m share plane 0 as
-// X_0 + i X_m, so the transform fills exactly m planes.
+// twist.  The two real bins kt = 0 and kt = m share plane 0 as X_0 + i X_m, so
+// the transform fills exactly m planes.
 // Forward t pass of the convolution from a column whose real input is in
 // LDS (xf, with xv[r] = xf[G r + s] in registers): R_z, packed real-to-complex
-// transform of length 2m, untangle, staged coalesced plane writes.
-template <int LOGM, bool PK>
-__device__ __forceinline__ void tfwd_conv_from_lds(float2* lds, const float2* tws,
-                                                   const float2* twc, const int4* srow,
-                                                   const float* sval, float (&xv)[TGeo<LOGM>::E],
-                                                   int tid, int col0, float2* __restrict__ spec,
-                                                   int nn) {
+// transform of length 2m, staged and untangled into the planes.  Only the
+// staging tile is shared by the block's waves: two barriers.
+template <int LOGM>
+__device__ __forceinline__ void tfwd_conv_from_lds(float2* lds, const TwTabs& tt, const float2* tws,
+                                                   const float2* twc,
+                                                   const float4* __restrict__ rows,
+                                                   float (&xv)[TGeo<LOGM>::E], int tid, int col0,
+                                                   float2* __restrict__ spec, int nn) {
   using T = TGeo<LOGM>;
   constexpr int M = 1 << LOGM, G = T::G, E = T::E, J = T::J, NT = T::NT;
   constexpr int ZS = M + M / 8 + 4;
   const int b = tid / G, s = tid % G;
-  float* xf = reinterpret_cast<float*>(lds + b * ZS);
-  float* pf = xf + M;
+  float2* slot = lds + b * ZS;
+  float* xf = reinterpret_cast<float*>(slot);
+  Prefix<LOGM>* pf = reinterpret_cast<Prefix<LOGM>*>(xf + M);
+  static_assert(resample_scan_rows(M, G) * G * sizeof(*pf) <= M * sizeof(float), "prefix sums fit");
+  float4 d[E];                                     // descriptors of the rows 2p, 2p + 1
+#pragma unroll
+  for (int r = 0; r < E; ++r) d[r] = rows[2 * (G * (r >> 1) + s) + (r & 1)];
+  FftTw<LOGM> tw;
+  tw.load_a(tt.fa, s);
   // R_z rows of more than 3 taps (small q, where a z bin spans many t bins)
   // have interior weights exactly 1, so they are computed as w x[k0] +
   // (P[k1] - P[k0 + 1]) + w' x[k1] from exclusive prefix sums P of the first
@@ -223,81 +360,58 @@ __device__ __forceinline__ void tfwd_conv_from_lds(float2* lds, const float2* tw
   // built); rows of at most 3 taps are summed directly.  No row loops, so no
   // lane waits for the longest row of its wave.
   constexpr int RS = resample_scan_rows(M, G);
-  float carry = 0.f;
+  Prefix<LOGM> carry = 0;
 #pragma unroll
   for (int r = 0; r < RS; ++r) {
-    float inc = xv[r];
+    Prefix<LOGM> inc = xv[r];
+    if constexpr (G == 64) {
+      inc = wave_scan(inc);
+      pf[G * r + s] = carry + (inc - (double)xv[r]);
+      const unsigned long long u = (unsigned long long)__double_as_longlong(inc);
+      const unsigned lo = __builtin_amdgcn_readlane((int)(unsigned)u, 63);
+      const unsigned hi = __builtin_amdgcn_readlane((int)(u >> 32), 63);
+      carry += __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+    } else {
 #pragma unroll
-    for (int d = 1; d < G; d <<= 1) {
-      const float y = __shfl_up(inc, d, G);
-      if (s >= d) inc += y;
+      for (int d1 = 1; d1 < G; d1 <<= 1) {
+        const float y = __shfl_up(inc, d1, G);
+        if (s >= d1) inc += y;
+      }
+      pf[G * r + s] = carry + (inc - xv[r]);
+      carry += __shfl(inc, G - 1, G);
     }
-    pf[G * r + s] = carry + (inc - xv[r]);
-    carry += __shfl(inc, G - 1, G);
   }
-  __syncthreads();
+  __builtin_amdgcn_wave_barrier();                 // a column belongs to one wave
   // R_z rows 2p, 2p+1 packed as one complex value, lower half of the transform
   float2 x[E];
 #pragma unroll
   for (int r = 0; r < E / 2; ++r) {
-    const int p = G * r + s;
-    float v[2];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) v[h] = rz_row(srow[2 * p + h], sval, xf, pf);
-    x[r] = make_float2(v[0], v[1]);
+    if (2 * G * r < resample_long_rows(M))
+      x[r] = make_float2(rz_row<true>(d[2 * r], xf, pf), rz_row<true>(d[2 * r + 1], xf, pf));
+    else
+      x[r] = make_float2(rz_row<false>(d[2 * r], xf, pf), rz_row<false>(d[2 * r + 1], xf, pf));
   }
-#pragma unroll
-  for (int r = 0; r < E / 2; ++r) x[r + E / 2] = cmul(x[r], tws[2 * (G * r + s)]);
-  dif_inlane<G, E, E / 4>(x, s, twc);
-  dif_xlane<G, E>(x, s, twc);
-  __syncthreads();                                 // every column's input consumed
-  float2* z = lds + b * ZS;
-#pragma unroll
-  for (int r = 0; r < E; ++r) z[zix(G * r + s)] = x[r];
+  __builtin_amdgcn_wave_barrier();
+  tw.load_b(tt.fb, s);
+  col_transform_fwd<LOGM, true, 1>(x, slot, tw, tws, twc, s);
+  __syncthreads();                                 // every column's LDS is free
+  stage_put<LOGM, J>(lds, x, b, s);
   __syncthreads();
-  // untangle the packed real transform: X[k] = 1/2 (Z_k + conj Z_{m-k}) - i/2 W^k (Z_k - conj Z_{m-k})
-  float2 X[E];
-  float2 XM = make_float2(0.f, 0.f);
-#pragma unroll
-  for (int r = 0; r <= E; ++r) {
-    const int k = r < E ? G * r + s : M;
-    if (r == E && s != 0) break;
-    const float2 zk = z[zix(brev(k & (M - 1), LOGM))];
-    const float2 zm = z[zix(brev((M - k) & (M - 1), LOGM))];
-    const float2 e = make_float2(0.5f * (zk.x + zm.x), 0.5f * (zk.y - zm.y));
-    const float2 o = make_float2(0.5f * (zk.x - zm.x), 0.5f * (zk.y + zm.y));
-    const float2 wk = k < M ? tws[k] : make_float2(-1.f, 0.f);
-    const float2 wo = cmul(wk, o);
-    const float2 v = make_float2(e.x + wo.y, e.y - wo.x);
-    if (r < E) X[r] = v; else XM = v;
-  }
-  // X_0 and X_m are real (their imaginary parts vanish identically)
-  if (PK && s == 0) X[0].y = XM.x;
-  __syncthreads();                                 // staging overwrites the columns
-#pragma unroll
-  for (int r = 0; r < E; ++r) lds[stg<J>(G * r + s, b)] = X[r];
-  if (!PK && s == 0) lds[stg<J>(M, b)] = XM;
-  __syncthreads();
-  lds_to_planes<J, NT, PK ? M : M + 1>(lds, spec, nn, col0, tid);
+  untangle_to_planes<J, NT, LOGM, 1>(lds, tt.tw, spec, nn, col0, tid);
 }
 
-template <int LOGM, bool PK>
-__global__ void __launch_bounds__(TGeo<LOGM>::NT)
-k_tfwd_conv(ConvSrc src, ResampleTables S, const float2* __restrict__ tw,
-            const float2* __restrict__ twcg, float2* __restrict__ spec, int nn, const DevCtl* ctl,
-            size_t zs, int gate) {
+template <int LOGM>
+__global__ void __launch_bounds__(TGeo<LOGM>::NT, t_waves(LOGM))
+k_tfwd_conv(ConvSrc src, ResampleTables S, TwTabs tt, float2* __restrict__ spec, int nn,
+            const DevCtl* ctl, size_t zs, int gate) {
   using T = TGeo<LOGM>;
   constexpr int M = 1 << LOGM, G = T::G, E = T::E, J = T::J, NT = T::NT;
   constexpr int ZS = M + M / 8 + 4;               // per-column LDS stride (float2)
-  constexpr int LDS2 = (J * ZS > stg_size<J>(M + 1)) ? J * ZS : stg_size<J>(M + 1);
-  // the resampling table (<= 3m + 64 values) is staged in LDS up to m = 1024
-  constexpr bool STAGE = M <= 1024;
-  constexpr int NNZ = STAGE ? 3 * M + 64 : 1;
+  constexpr int LDS2 = (J * ZS > stg_size<J>(M)) ? J * ZS : stg_size<J>(M);
+  constexpr bool OLD = !FftCol<LOGM>::PASS;
   __shared__ float2 lds[LDS2];
-  __shared__ float2 tws[M];
-  __shared__ float2 twc[M];
-  __shared__ int4 srow_l[STAGE ? M : 1];
-  __shared__ float sval_l[NNZ];
+  __shared__ float2 tws[OLD ? M : 1];
+  __shared__ float2 twc[OLD ? M : 1];
   const size_t zo = (size_t)blockIdx.z * zs;
   ctl = zsh(ctl, zo);
   const CtlHead hd = ctl_head(ctl);
@@ -305,9 +419,8 @@ k_tfwd_conv(ConvSrc src, ResampleTables S, const float2* __restrict__ tw,
   const float* sb = vol_in(src.b, hd, zo);
   const float* sc_ = vol_in(src.c, hd, zo);
   if (gated_off(hd, gate)) return;
-  zsh_tables(S, zo);
-  tw = zsh(tw, zo);
-  twcg = zsh(twcg, zo);
+  S.rows = zsh(S.rows, zo);
+  zsh_tw(tt, zo);
   spec = zsh(spec, zo);
   src.w = zsh(src.w, zo);
   src.mask = zsh(src.mask, zo);
@@ -316,18 +429,12 @@ k_tfwd_conv(ConvSrc src, ResampleTables S, const float2* __restrict__ tw,
   const int col0 = xcd_block(blockIdx.x, gridDim.x) * J, col = col0 + b;
   // the tables' loads issue with the operands' (one round trip for both);
   // they reach LDS after the operands are loaded
-  auto t_tws = table_copy<NT, M>(tws, tw);
-  auto t_twc = table_copy<NT, M>(twc, twcg);
-  auto t_row = table_copy<NT, STAGE ? M : 1>(srow_l, S.rows);
-  auto t_val = table_copy<NT, NNZ>(sval_l, S.rvals);
-  t_tws.load(tid);
-  t_twc.load(tid);
-  if constexpr (STAGE) {
-    t_row.load(tid);
-    t_val.load(tid);
+  auto t_tws = table_copy<NT, OLD ? M : 1>(tws, tt.tw);
+  auto t_twc = table_copy<NT, OLD ? M : 1>(twc, tt.twc);
+  if constexpr (OLD) {
+    t_tws.load(tid);
+    t_twc.load(tid);
   }
-  const int4* srow = STAGE ? srow_l : S.rows;
-  const float* sval = STAGE ? sval_l : S.rvals;
 
   float ca = 1.f, cb = 0.f;
   if (src.lincache) {
@@ -355,11 +462,9 @@ k_tfwd_conv(ConvSrc src, ResampleTables S, const float2* __restrict__ tw,
     vc[r] = pc[g];
     vw[r] = pw[k];
   }
-  t_tws.store(tid);
-  t_twc.store(tid);
-  if constexpr (STAGE) {
-    t_row.store(tid);
-    t_val.store(tid);
+  if constexpr (OLD) {
+    t_tws.store(tid);
+    t_twc.store(tid);
   }
   float xv[E];
 #pragma unroll
@@ -372,25 +477,45 @@ k_tfwd_conv(ConvSrc src, ResampleTables S, const float2* __restrict__ tw,
     xv[r] = x * sc * mk;
     xf[k] = xv[r];
   }
-  tfwd_conv_from_lds<LOGM, PK>(lds, tws, twc, srow, sval, xv, tid, col0, spec, nn);
+  if constexpr (OLD) __syncthreads();              // the tables
+  tfwd_conv_from_lds<LOGM>(lds, tt, tws, twc, S.rows, xv, tid, col0, spec, nn);
+}
+
+// A column's inverse transform up to its m real samples g2 (packed pairs) in
+// LDS: spectrum from the staging tile, transform, crop.  g2 of column b is at
+// lds + b (m/2 + 2).
+template <int LOGM>
+__device__ __forceinline__ float2* tinv_conv_samples(float2* lds, const FftTw<LOGM>& tw,
+                                                     const float2* tws, const float2* twc,
+                                                     float scale, int b, int s) {
+  using T = TGeo<LOGM>;
+  constexpr int M = 1 << LOGM, G = T::G, E = T::E, J = T::J, ZS = M + M / 8 + 4;
+  float2 x[E];
+  stage_get<LOGM, J>(lds, x, b, s);
+  __syncthreads();                                 // staging consumed: the columns' LDS
+  col_transform_inv<LOGM, true, 1>(x, lds + b * ZS, tw, tws, twc, s);
+  if constexpr (FftCol<LOGM>::PASS) __syncthreads();   // every column's exchanges are done
+  float2* g2 = lds + b * (M / 2 + 2);
+#pragma unroll
+  for (int r = 0; r < E / 2; ++r) g2[G * r + s] = cscale(x[r], scale);
+  __builtin_amdgcn_wave_barrier();                 // a column belongs to one wave
+  return g2;
 }
 
 // t pass, inverse, convolution: planes -> C2R (length 2m) -> crop -> S^T -> epilogue
-// (PK: plane 0 holds X_0 + i X_m, as written by the forward pass)
-template <int LOGM, int EPI, bool PK>
-__global__ void __launch_bounds__(TGeo<LOGM>::NT)
-k_tinv_conv(const float2* __restrict__ spec, int nn, ResampleTables S,
-            const float2* __restrict__ tw, const float2* __restrict__ twcg, ConvEpi ep, float scale,
-            const DevCtl* ctl, size_t zs, int gate) {
+// (plane 0 holds X_0 + i X_m, as written by the forward pass)
+template <int LOGM, int EPI>
+__global__ void __launch_bounds__(TGeo<LOGM>::NT, t_waves(LOGM))
+k_tinv_conv(const float2* __restrict__ spec, int nn, ResampleTables S, TwTabs tt, ConvEpi ep,
+            float scale, const DevCtl* ctl, size_t zs, int gate) {
   using T = TGeo<LOGM>;
-  constexpr int M = 1 << LOGM, H = M / 2, G = T::G, E = T::E, J = T::J, NT = T::NT;
-  constexpr bool STAGE = M <= 1024;
-  constexpr int NNZ = STAGE ? 3 * M + 64 : 1;
-  __shared__ float2 lds[stg_size<J>(M + 1)];
-  __shared__ float2 tws[M];
-  __shared__ float2 twc[M];
-  __shared__ int4 scol_l[STAGE ? M : 1];
-  __shared__ float sval_l[NNZ];
+  constexpr int M = 1 << LOGM, G = T::G, E = T::E, J = T::J, NT = T::NT;
+  constexpr int ZS = M + M / 8 + 4;
+  constexpr int LDS2 = (J * ZS > stg_size<J>(M)) ? J * ZS : stg_size<J>(M);
+  constexpr bool OLD = !FftCol<LOGM>::PASS;
+  __shared__ float2 lds[LDS2];
+  __shared__ float2 tws[OLD ? M : 1];
+  __shared__ float2 twc[OLD ? M : 1];
   const size_t zo = (size_t)blockIdx.z * zs;
   ctl = zsh(ctl, zo);
   const CtlHead hd = ctl_head(ctl);
@@ -399,9 +524,8 @@ k_tinv_conv(const float2* __restrict__ spec, int nn, ResampleTables S,
   const float* eaup =
       (EPI == EPI_FWD_OBJ || EPI == EPI_FWD_DUAL) ? vol_in(ep.au_prev, hd, zo) : nullptr;
   if (gated_off(hd, gate)) return;
-  zsh_tables(S, zo);
-  tw = zsh(tw, zo);
-  twcg = zsh(twcg, zo);
+  S.cols = zsh(S.cols, zo);
+  zsh_tw(tt, zo);
   spec = zsh(spec, zo);
   ep.w = zsh(ep.w, zo);
   ep.mask = zsh(ep.mask, zo);
@@ -409,45 +533,18 @@ k_tinv_conv(const float2* __restrict__ spec, int nn, ResampleTables S,
   ep.partials = zsh(ep.partials, zo);
   const int tid = threadIdx.x, b = tid / G, s = tid % G;
   const int col0 = xcd_block(blockIdx.x, gridDim.x) * J, col = col0 + b;
+  FftTw<LOGM> tw;
   // tables and the block's planes: one round trip
-  if constexpr (STAGE)
-    copy_together(tid, table_copy<NT, M>(tws, tw), table_copy<NT, M>(twc, twcg),
-                  table_copy<NT, M>(scol_l, S.cols), table_copy<NT, NNZ>(sval_l, S.cvals),
-                  planes_copy<J, NT, PK ? M : M + 1>(lds, spec, nn, col0));
+  if constexpr (OLD)
+    copy_together(tid, table_copy<NT, M>(tws, tt.tw), table_copy<NT, M>(twc, tt.twc),
+                  tangle_copy<J, NT, LOGM, 1>(lds, spec, tt.tw, nn, col0));
   else
-    copy_together(tid, table_copy<NT, M>(tws, tw), table_copy<NT, M>(twc, twcg),
-                  planes_copy<J, NT, PK ? M : M + 1>(lds, spec, nn, col0));
-  const int4* scol = STAGE ? scol_l : S.cols;
-  const float* sval = STAGE ? sval_l : S.cvals;
+    copy_together(tid, tangle_copy<J, NT, LOGM, 1>(lds, spec, tt.tw, nn, col0));
+  tw.load_b(tt.fb, s);
+  tw.load_a(tt.fa, s);
   __syncthreads();
-  // packed even/odd spectrum at this lane's bit-reversed positions:
-  // Z[k] = 1/2 (X_k + conj X_{m-k}) + i/2 conj(W^k) (X_k - conj X_{m-k})
-  float2 x[E];
-#pragma unroll
-  for (int r = 0; r < E; ++r) {
-    const int k = brev(G * r + s, LOGM);
-    float2 Xk = lds[stg<J>(k, b)];
-    float2 Xm = lds[stg<J>(PK ? (M - k) & (M - 1) : M - k, b)];
-    if (PK && k == 0) {
-      Xm = make_float2(Xk.y, 0.f);
-      Xk.y = 0.f;
-    }
-    const float2 e = make_float2(0.5f * (Xk.x + Xm.x), 0.5f * (Xk.y - Xm.y));
-    const float2 o = make_float2(0.5f * (Xk.x - Xm.x), 0.5f * (Xk.y + Xm.y));
-    const float2 wo = cmulc(o, tws[k]);
-    x[r] = make_float2(e.x - wo.y, e.y + wo.x);
-  }
-  dit_xlane<G, E>(x, s, twc);
-  dit_inlane<G, E, E / 4>(x, s, twc);
-  // last stage (span m/2), lower half only: the crop to the first m samples
-#pragma unroll
-  for (int r = 0; r < E / 2; ++r) x[r] = cadd(x[r], cmulc(x[r + E / 2], tws[2 * (G * r + s)]));
-  __syncthreads();                                 // staging consumed
-  float2* g2 = lds + b * (H + 2);                  // this column's real samples, packed
-#pragma unroll
-  for (int r = 0; r < E / 2; ++r) g2[G * r + s] = cscale(x[r], scale);
-  __syncthreads();
-  const float* g = reinterpret_cast<const float*>(g2);
+  const float* g = reinterpret_cast<const float*>(
+      tinv_conv_samples<LOGM>(lds, tw, tws, twc, scale, b, s));
   double acc0 = 0.0, acc1 = 0.0;
   float ca = 1.f, cb = 0.f;
   if (EPI == EPI_FWD_OBJ || EPI == EPI_FWD_DUAL) {
@@ -461,10 +558,12 @@ k_tinv_conv(const float2* __restrict__ spec, int nn, ResampleTables S,
   const bool hw = ep.w != nullptr;
   const float* pw = hw ? ep.w : eout + (size_t)col * M;
   float vw[E], vau[E], vaup[E], vt0[E];
+  float4 sc[E];
 #pragma unroll
   for (int r = 0; r < E; ++r) {
     const int k = G * r + s;
     const size_t gi = (size_t)col * M + k;
+    sc[r] = S.cols[k];
     vw[r] = pw[k];
     if constexpr (EPI == EPI_FWD_OBJ || EPI == EPI_FWD_DUAL) {
       vau[r] = eau[gi];
@@ -475,7 +574,7 @@ k_tinv_conv(const float2* __restrict__ spec, int nn, ResampleTables S,
 #pragma unroll
   for (int r = 0; r < E; ++r) {
     const int k = G * r + s;
-    float tk = st_taps(scol[k], sval, g);
+    float tk = st_taps(sc[r], g);
     tk *= hw ? vw[r] : 1.f;
     const size_t gi = (size_t)col * M + k;
     if (EPI == EPI_PLAIN || EPI == EPI_NORM) {
@@ -756,9 +855,16 @@ __device__ __forceinline__ void row_put(const float2 (&x)[E], float2* __restrict
     put32(q, p0 + E * c, x[c]);
   } else {
 #pragma unroll
-    for (int i = 0; i < E / 4; i += 2)
-      *reinterpret_cast<float4*>(reinterpret_cast<char*>(q) + ((p0 + E * c + i) << 3)) =
-          make_float4(x[4 * i + c].x, x[4 * i + c].y, x[4 * i + 4 + c].x, x[4 * i + 4 + c].y);
+    for (int i = 0; i < E / 4; i += 2) {
+      typedef float f4 __attribute__((ext_vector_type(4)));
+      const f4 v = {x[4 * i + c].x, x[4 * i + c].y, x[4 * i + 4 + c].x, x[4 * i + 4 + c].y};
+      f4* to = reinterpret_cast<f4*>(reinterpret_cast<char*>(q) + ((p0 + E * c + i) << 3));
+      // n <= 64: past L2, where the lines would only wait for the t pass that
+      // reads them on other XCDs (64x64x512: 24.0 -> 22.6 us; n = 128 reads its
+      // first half back: 121 -> 123)
+      if constexpr (E < 32) __builtin_nontemporal_store(v, to);
+      else *to = v;
+    }
   }
 }
 // this lane's kernel values of half H, from place `first` of the plane on
@@ -1360,66 +1466,37 @@ __device__ __forceinline__ void rhs_pairs(float2 (&x)[E], const RhsSrc& rs, cons
 
 // Forward t pass of a diagonal solve from the right-hand side in registers
 // (x[r] = bins 2p, 2p + 1, p = G r + s): complex transform of length m/2,
-// untangle, planes kt = 0 .. m/2 - 1 (bins 0 and m/2 packed in plane 0),
-// staged coalesced writes.  J columns per block; waves with !act only meet
-// the barriers.
+// planes kt = 0 .. m/2 - 1 (bins 0 and m/2 packed in plane 0).  J columns per
+// block; waves with !act only meet the barriers.
 template <int LOGM, int J, int NT>
 __device__ __forceinline__ void tfwd_solve_from_regs(float2 (&x)[TGeo<LOGM - 1>::E], bool act,
-                                                     float2* lds, const float2* tws,
+                                                     float2* lds, const FftTw<LOGM - 1>& tw,
+                                                     const TwTabs& tt, const float2* tws,
                                                      const float2* twc, int tid, int col0,
                                                      float2* __restrict__ spec, int nn) {
   using T = TGeo<LOGM - 1>;
   constexpr int M = 1 << LOGM, H = M / 2, LOGH = LOGM - 1;
-  constexpr int G = T::G, E = T::E, ZS = H + H / 8 + 4;
+  constexpr int G = T::G, ZS = H + H / 8 + 4;
   const int b = tid / G, s = tid % G;
   __syncthreads();
-  float2* z = lds + b * ZS;
-  if (act) {
-    dif_inlane<G, E, E / 2>(x, s, twc);
-    dif_xlane<G, E>(x, s, twc);
-#pragma unroll
-    for (int r = 0; r < E; ++r) z[zix(G * r + s)] = x[r];
-  }
+  if (act) col_transform_fwd<LOGH, false, 2>(x, lds + b * ZS, tw, tws, twc, s);
+  if constexpr (FftCol<LOGH>::PASS) __syncthreads();   // every column's exchanges are done
+  if (act) stage_put<LOGH, J>(lds, x, b, s);
   __syncthreads();
-  float2 X[E];
-  if (act) {
-    float2 XH = make_float2(0.f, 0.f);
-#pragma unroll
-    for (int r = 0; r <= E; ++r) {
-      const int k = r < E ? G * r + s : H;
-      if (r == E && s != 0) break;
-      const float2 zk = z[zix(brev(k & (H - 1), LOGH))];
-      const float2 zm = z[zix(brev((H - k) & (H - 1), LOGH))];
-      const float2 e = make_float2(0.5f * (zk.x + zm.x), 0.5f * (zk.y - zm.y));
-      const float2 o = make_float2(0.5f * (zk.x - zm.x), 0.5f * (zk.y + zm.y));
-      const float2 wk = k < H ? tws[2 * k] : make_float2(-1.f, 0.f);
-      const float2 wo = cmul(wk, o);
-      const float2 v = make_float2(e.x + wo.y, e.y - wo.x);
-      if (r < E) X[r] = v; else XH = v;
-    }
-    if (s == 0) X[0].y = XH.x;
-  }
-  __syncthreads();
-  if (act) {
-#pragma unroll
-    for (int r = 0; r < E; ++r) lds[stg<J>(G * r + s, b)] = X[r];
-  }
-  __syncthreads();
-  lds_to_planes<J, NT, H>(lds, spec, nn, col0, tid);
+  untangle_to_planes<J, NT, LOGH, 2>(lds, tt.tw, spec, nn, col0, tid);
 }
 
 template <int LOGM, int SRC>
 __global__ void __launch_bounds__(TGeo<LOGM - 1>::NT)
-k_tfwd_solve(const float* __restrict__ src, RhsSrc rs, const float2* __restrict__ tw,
-             const float2* __restrict__ twcg, float2* __restrict__ spec, int nn, DevCtl* ctl,
-             size_t zs, int gate) {
+k_tfwd_solve(const float* __restrict__ src, RhsSrc rs, TwTabs tt, float2* __restrict__ spec, int nn,
+             DevCtl* ctl, size_t zs, int gate) {
   using T = TGeo<LOGM - 1>;
   constexpr int M = 1 << LOGM, H = M / 2, LOGH = LOGM - 1;
   constexpr int G = T::G, E = T::E, J = T::J, NT = T::NT, ZS = H + H / 8 + 4;
-  constexpr int LDS2 = (J * ZS > stg_size<J>(H + 1)) ? J * ZS : stg_size<J>(H + 1);
+  constexpr int LDS2 = (J * ZS > stg_size<J>(H)) ? J * ZS : stg_size<J>(H);
+  constexpr bool OLD = !FftCol<LOGH>::PASS;
   __shared__ float2 lds[LDS2];
-  __shared__ float2 tws[M];
-  __shared__ float2 twc[H];
+  __shared__ float2 twc[OLD ? H : 1];
   const size_t zo = (size_t)blockIdx.z * zs;
   ctl = zsh(ctl, zo);
   const CtlHead hd = ctl_head(ctl);
@@ -1427,16 +1504,13 @@ k_tfwd_solve(const float* __restrict__ src, RhsSrc rs, const float2* __restrict_
   const float* au = SRC == RHS_TAU ? vol_resolve(rs.au, hd, zo) : nullptr;
   if (gated_off(hd, gate)) return;
   if ((gate & G_FIRST) && blockIdx.x == 0 && threadIdx.x == 0) ctl->reject = 0;
-  tw = zsh(tw, zo);
-  twcg = zsh(twcg, zo);
+  zsh_tw(tt, zo);
   spec = zsh(spec, zo);
   const int tid = threadIdx.x, b = tid / G, s = tid % G;
   const int col0 = xcd_block(blockIdx.x, gridDim.x) * J, col = col0 + b;
-  // the tables' loads issue with the operands' (one round trip for both)
-  auto t_tws = table_copy<NT, M>(tws, tw);
-  auto t_twc = table_copy<NT, H>(twc, twcg);
-  t_tws.load(tid);
-  t_twc.load(tid);
+  // the table's loads issue with the operands' (one round trip for both)
+  auto t_twc = table_copy<NT, OLD ? H : 1>(twc, tt.twc);
+  if constexpr (OLD) t_twc.load(tid);
   float2 x[E];
   if constexpr (SRC == RHS_LOAD) {
     src = zsh(src, zo);
@@ -1455,24 +1529,26 @@ k_tfwd_solve(const float* __restrict__ src, RhsSrc rs, const float2* __restrict_
     rhs_pairs<SRC, G, E, J, M, NT>(x, rs, ctl, xb, au, col0, b, s, tid, nn,
                                    reinterpret_cast<float*>(lds));
   }
-  t_tws.store(tid);
-  t_twc.store(tid);
-  tfwd_solve_from_regs<LOGM, J, NT>(x, true, lds, tws, twc, tid, col0, spec, nn);
+  if constexpr (OLD) t_twc.store(tid);
+  FftTw<LOGH> tw;
+  tw.load_a(tt.fa + FftCol<LOGM>::TA, s);
+  tw.load_b(tt.fb + FftCol<LOGM>::TB, s);
+  tfwd_solve_from_regs<LOGM, J, NT>(x, true, lds, tw, tt, nullptr, twc, tid, col0, spec, nn);
 }
 
 // t pass, inverse, diagonal solve: planes kt = 0 .. m/2 - 1 (plane 0 packed
 // as above) -> C2R (length m).
 template <int LOGM>
 __global__ void __launch_bounds__(TGeo<LOGM - 1>::NT)
-k_tinv_solve(const float2* __restrict__ spec, int nn, const float2* __restrict__ tw,
-             const float2* __restrict__ twcg, SolveEpi ep, float scale, const DevCtl* ctl,
-             size_t zs, int gate) {
+k_tinv_solve(const float2* __restrict__ spec, int nn, TwTabs tt, SolveEpi ep, float scale,
+             const DevCtl* ctl, size_t zs, int gate) {
   using T = TGeo<LOGM - 1>;
   constexpr int M = 1 << LOGM, H = M / 2, LOGH = LOGM - 1;
-  constexpr int G = T::G, E = T::E, J = T::J, NT = T::NT;
-  __shared__ float2 lds[stg_size<J>(H + 1)];
-  __shared__ float2 tws[M];
-  __shared__ float2 twc[H];
+  constexpr int G = T::G, E = T::E, J = T::J, NT = T::NT, ZS = H + H / 8 + 4;
+  constexpr int LDS2 = (J * ZS > stg_size<J>(H)) ? J * ZS : stg_size<J>(H);
+  constexpr bool OLD = !FftCol<LOGH>::PASS;
+  __shared__ float2 lds[LDS2];
+  __shared__ float2 twc[OLD ? H : 1];
   const size_t zo = (size_t)blockIdx.z * zs;
   ctl = zsh(ctl, zo);
   const CtlHead hd = ctl_head(ctl);
@@ -1480,31 +1556,23 @@ k_tinv_solve(const float2* __restrict__ spec, int nn, const float2* __restrict__
   const float* eref = vol_in(ep.ref, hd, zo);
   if (gated_off(hd, gate)) return;
   spec = zsh(spec, zo);
-  tw = zsh(tw, zo);
-  twcg = zsh(twcg, zo);
+  zsh_tw(tt, zo);
   ep.partials = zsh(ep.partials, zo);
   const int tid = threadIdx.x, b = tid / G, s = tid % G;
   const int col0 = xcd_block(blockIdx.x, gridDim.x) * J, col = col0 + b;
-  copy_together(tid, table_copy<NT, M>(tws, tw), table_copy<NT, H>(twc, twcg),
-                planes_copy<J, NT, H>(lds, spec, nn, col0));
+  if constexpr (OLD)
+    copy_together(tid, table_copy<NT, H>(twc, tt.twc),
+                  tangle_copy<J, NT, LOGH, 2>(lds, spec, tt.tw, nn, col0));
+  else
+    copy_together(tid, tangle_copy<J, NT, LOGH, 2>(lds, spec, tt.tw, nn, col0));
+  FftTw<LOGH> tw;
+  tw.load_b(tt.fb + FftCol<LOGM>::TB, s);
+  tw.load_a(tt.fa + FftCol<LOGM>::TA, s);
   __syncthreads();
   float2 x[E];
-#pragma unroll
-  for (int r = 0; r < E; ++r) {
-    const int k = brev(G * r + s, LOGH);
-    float2 Xk = lds[stg<J>(k, b)];
-    float2 Xm = lds[stg<J>((H - k) & (H - 1), b)];
-    if (k == 0) {
-      Xm = make_float2(Xk.y, 0.f);
-      Xk.y = 0.f;
-    }
-    const float2 e = make_float2(0.5f * (Xk.x + Xm.x), 0.5f * (Xk.y - Xm.y));
-    const float2 o = make_float2(0.5f * (Xk.x - Xm.x), 0.5f * (Xk.y + Xm.y));
-    const float2 wo = cmulc(o, tws[2 * k]);
-    x[r] = make_float2(e.x - wo.y, e.y + wo.x);
-  }
-  dit_xlane<G, E>(x, s, twc);
-  dit_inlane<G, E, E / 2>(x, s, twc);
+  stage_get<LOGH, J>(lds, x, b, s);
+  if constexpr (!OLD) __syncthreads();             // staging consumed: the columns' LDS
+  col_transform_inv<LOGH, false, 2>(x, lds + b * ZS, tw, nullptr, twc, s);
   float2* out2 = reinterpret_cast<float2*>(eout) + (size_t)col * H;
   if (!eref) {
 #pragma unroll
@@ -1543,31 +1611,28 @@ k_tinv_solve(const float2* __restrict__ spec, int nn, const float2* __restrict__
 // launch does not change.  Block geometry of the convolution pass; the solve
 // phase runs on J x G_s threads (whole waves).  The spectrum buffer is
 // reused in place.
-template <int LOGM, bool PK, int EPI>
-__global__ void __launch_bounds__(TGeo<LOGM>::NT)
-k_tinv_conv_rhs(float2* __restrict__ spec, int nn, ResampleTables S,
-                const float2* __restrict__ tw, const float2* __restrict__ twcg, ConvEpi ep,
+template <int LOGM, int EPI>
+__global__ void __launch_bounds__(TGeo<LOGM>::NT, t_waves(LOGM))
+k_tinv_conv_rhs(float2* __restrict__ spec, int nn, ResampleTables S, TwTabs tt, ConvEpi ep,
                 float scale, RhsSrc rs, DevCtl* ctl, size_t zs, int gate) {
   static_assert(EPI == EPI_PLAIN || EPI == EPI_FWD_DUAL, "fused epilogues");
   constexpr int SRC = EPI == EPI_PLAIN ? RHS_U : RHS_TAU;
   using T = TGeo<LOGM>;
   using TS = TGeo<LOGM - 1>;
-  constexpr int M = 1 << LOGM, H = M / 2, G = T::G, E = T::E, J = T::J, NT = T::NT;
+  constexpr int M = 1 << LOGM, G = T::G, E = T::E, J = T::J, NT = T::NT;
   constexpr int GS = TS::G, ES = TS::E;
   static_assert(J * GS <= NT && (J * GS) % 64 == 0, "solve phase on whole waves");
   constexpr int ZS = M + M / 8 + 4;
-  constexpr int LDS2 = (J * ZS > stg_size<J>(M + 1)) ? J * ZS : stg_size<J>(M + 1);
+  constexpr int LDS2 = (J * ZS > stg_size<J>(M)) ? J * ZS : stg_size<J>(M);
   // LDS as floats: the C2R samples [0, J (m + 4)), the p_y rows of the
   // right-hand side [0, (J + 1) m), grad f at the top [2 LDS2 - J m, 2 LDS2)
   static_assert(2 * LDS2 >= J * (2 * M + 4) && 2 * LDS2 >= (2 * J + 1) * M, "LDS regions");
   constexpr int GFL = 2 * LDS2 - J * M;
-  constexpr bool STAGE = M <= 1024;
-  constexpr int NNZ = STAGE ? 3 * M + 64 : 1;
+  constexpr bool OLD = !FftCol<LOGM>::PASS, OLDS = !FftCol<LOGM - 1>::PASS;
+  constexpr int NTWC = OLD ? M : OLDS ? M / 2 : 1;
   __shared__ float2 lds[LDS2];
-  __shared__ float2 tws[M];
-  __shared__ float2 twc[M];
-  __shared__ int4 scol_l[STAGE ? M : 1];
-  __shared__ float sval_l[NNZ];
+  __shared__ float2 tws[OLD ? M : 1];
+  __shared__ float2 twc[NTWC];
   const size_t zo = (size_t)blockIdx.z * zs;
   ctl = zsh(ctl, zo);
   const CtlHead hd = ctl_head(ctl);
@@ -1577,9 +1642,8 @@ k_tinv_conv_rhs(float2* __restrict__ spec, int nn, ResampleTables S,
   const float* eaup = EPI == EPI_FWD_DUAL ? vol_in(ep.au_prev, hd, zo) : nullptr;
   if (gated_off(hd, gate)) return;
   if ((gate & G_FIRST) && blockIdx.x == 0 && threadIdx.x == 0) ctl->reject = 0;
-  zsh_tables(S, zo);
-  tw = zsh(tw, zo);
-  twcg = zsh(twcg, zo);
+  S.cols = zsh(S.cols, zo);
+  zsh_tw(tt, zo);
   spec = zsh(spec, zo);
   ep.w = zsh(ep.w, zo);
   ep.mask = zsh(ep.mask, zo);
@@ -1592,44 +1656,22 @@ k_tinv_conv_rhs(float2* __restrict__ spec, int nn, ResampleTables S,
   const int tid = threadIdx.x, b = tid / G, s = tid % G;
   const int col0 = xcd_block(blockIdx.x, gridDim.x) * J, col = col0 + b;
   // tables and the block's planes: one round trip
-  if constexpr (STAGE)
-    copy_together(tid, table_copy<NT, M>(tws, tw), table_copy<NT, M>(twc, twcg),
-                  table_copy<NT, M>(scol_l, S.cols), table_copy<NT, NNZ>(sval_l, S.cvals),
-                  planes_copy<J, NT, PK ? M : M + 1>(lds, spec, nn, col0));
+  if constexpr (OLD)
+    copy_together(tid, table_copy<NT, M>(tws, tt.tw), table_copy<NT, NTWC>(twc, tt.twc),
+                  tangle_copy<J, NT, LOGM, 1>(lds, spec, tt.tw, nn, col0));
+  else if constexpr (OLDS)
+    copy_together(tid, table_copy<NT, NTWC>(twc, tt.twc),
+                  tangle_copy<J, NT, LOGM, 1>(lds, spec, tt.tw, nn, col0));
   else
-    copy_together(tid, table_copy<NT, M>(tws, tw), table_copy<NT, M>(twc, twcg),
-                  planes_copy<J, NT, PK ? M : M + 1>(lds, spec, nn, col0));
-  const int4* scol = STAGE ? scol_l : S.cols;
-  const float* sval = STAGE ? sval_l : S.cvals;
-  __syncthreads();
-  // adjoint inverse t pass (as k_tinv_conv, plain epilogue)
-  float2 x[E];
-#pragma unroll
-  for (int r = 0; r < E; ++r) {
-    const int k = brev(G * r + s, LOGM);
-    float2 Xk = lds[stg<J>(k, b)];
-    float2 Xm = lds[stg<J>(PK ? (M - k) & (M - 1) : M - k, b)];
-    if (PK && k == 0) {
-      Xm = make_float2(Xk.y, 0.f);
-      Xk.y = 0.f;
-    }
-    const float2 e = make_float2(0.5f * (Xk.x + Xm.x), 0.5f * (Xk.y - Xm.y));
-    const float2 o = make_float2(0.5f * (Xk.x - Xm.x), 0.5f * (Xk.y + Xm.y));
-    const float2 wo = cmulc(o, tws[k]);
-    x[r] = make_float2(e.x - wo.y, e.y + wo.x);
-  }
-  dit_xlane<G, E>(x, s, twc);
-  dit_inlane<G, E, E / 4>(x, s, twc);
-#pragma unroll
-  for (int r = 0; r < E / 2; ++r) x[r] = cadd(x[r], cmulc(x[r + E / 2], tws[2 * (G * r + s)]));
-  __syncthreads();                                 // staging consumed
-  float2* g2 = lds + b * (H + 2);
-#pragma unroll
-  for (int r = 0; r < E / 2; ++r) g2[G * r + s] = cscale(x[r], scale);
-  __syncthreads();
+    copy_together(tid, tangle_copy<J, NT, LOGM, 1>(lds, spec, tt.tw, nn, col0));
   float* gfl = reinterpret_cast<float*>(lds) + GFL;
   {
-    const float* g = reinterpret_cast<const float*>(g2);
+    FftTw<LOGM> tw;
+    tw.load_b(tt.fb, s);
+    tw.load_a(tt.fa, s);
+    __syncthreads();
+    const float* g = reinterpret_cast<const float*>(
+        tinv_conv_samples<LOGM>(lds, tw, tws, twc, scale, b, s));
     const float mk = ep.mask ? (float)ep.mask[col] : 1.f;
     float ca = 1.f, cb = 0.f;
     if constexpr (EPI == EPI_FWD_DUAL) {
@@ -1642,9 +1684,11 @@ k_tinv_conv_rhs(float2* __restrict__ spec, int nn, ResampleTables S,
     const bool hw = ep.w != nullptr;
     const float* pw = hw ? ep.w : xb + (size_t)col * M;
     float vw[E], vau[E], vaup[E];
+    float4 sc[E];
 #pragma unroll
     for (int r = 0; r < E; ++r) {
       const int k = G * r + s;
+      sc[r] = S.cols[k];
       vw[r] = pw[k];
       if constexpr (EPI == EPI_FWD_DUAL) {
         const size_t gi = (size_t)col * M + k;
@@ -1655,7 +1699,7 @@ k_tinv_conv_rhs(float2* __restrict__ spec, int nn, ResampleTables S,
 #pragma unroll
     for (int r = 0; r < E; ++r) {
       const int k = G * r + s;
-      float tk = st_taps(scol[k], sval, g);
+      float tk = st_taps(sc[r], g);
       tk *= hw ? vw[r] : 1.f;
       if constexpr (EPI == EPI_PLAIN) {
         gfl[b * M + k] = tk * mk;
@@ -1680,21 +1724,23 @@ k_tinv_conv_rhs(float2* __restrict__ spec, int nn, ResampleTables S,
   float2 y[ES];
   rhs_pairs<SRC, GS, ES, J, M, NT, true>(y, rs, ctl, xb, nullptr, col0, bs, ss, tid, nn,
                                          reinterpret_cast<float*>(lds), gfl, sact);
-  tfwd_solve_from_regs<LOGM, J, NT>(y, sact, lds, tws, twc, tid, col0, spec, nn);
+  FftTw<LOGM - 1> tws_;
+  tws_.load_a(tt.fa + FftCol<LOGM>::TA, ss);
+  tws_.load_b(tt.fb + FftCol<LOGM>::TB, ss);
+  tfwd_solve_from_regs<LOGM, J, NT>(y, sact, lds, tws_, tt, tws, twc, tid, col0, spec, nn);
 }
 
 // Inverse t pass of the u solve fused with the forward t pass of the
 // convolution that follows it (A u+, Algorithms 1 and 2): the solve's real
 // output column stays in LDS as the convolution's input, so u+ is not read
-// back and one launch and one table staging are saved.  Both passes work on
-// the same scan columns, so the spectrum buffer is reused in place (a block
-// reads its columns' solve planes before it writes their convolution
-// planes).  The block has the convolution pass's geometry (J columns, NT
-// threads); the solve phase runs on J x G_s of them (whole waves).
-template <int LOGM, bool PK>
-__global__ void __launch_bounds__(TGeo<LOGM>::NT)
-k_tinv_solve_fwd(float2* __restrict__ spec, int nn, ResampleTables S,
-                 const float2* __restrict__ tw, const float2* __restrict__ twcg, SolveEpi ep,
+// back and one launch is saved.  Both passes work on the same scan columns, so
+// the spectrum buffer is reused in place (a block reads its columns' solve
+// planes before it writes their convolution planes).  The block has the
+// convolution pass's geometry (J columns, NT threads); the solve phase runs on
+// J x G_s of them (whole waves).
+template <int LOGM>
+__global__ void __launch_bounds__(TGeo<LOGM>::NT, t_waves(LOGM))
+k_tinv_solve_fwd(float2* __restrict__ spec, int nn, ResampleTables S, TwTabs tt, SolveEpi ep,
                  float scale, const DevCtl* ctl, size_t zs, int gate) {
   using T = TGeo<LOGM>;
   using TS = TGeo<LOGM - 1>;
@@ -1703,64 +1749,46 @@ k_tinv_solve_fwd(float2* __restrict__ spec, int nn, ResampleTables S,
   constexpr int GS = TS::G, ES = TS::E;
   static_assert(J * GS <= NT && (J * GS) % 64 == 0, "solve phase on whole waves");
   constexpr int ZS = M + M / 8 + 4;
-  constexpr int LDS2 = (J * ZS > stg_size<J>(M + 1)) ? J * ZS : stg_size<J>(M + 1);
-  static_assert(stg_size<J>(H + 1) <= LDS2, "solve staging fits");
-  constexpr bool STAGE = M <= 1024;
-  constexpr int NNZ = STAGE ? 3 * M + 64 : 1;
+  constexpr int LDS2 = (J * ZS > stg_size<J>(M)) ? J * ZS : stg_size<J>(M);
+  static_assert(stg_size<J>(H) <= LDS2, "solve staging fits");
+  constexpr bool OLD = !FftCol<LOGM>::PASS, OLDS = !FftCol<LOGH>::PASS;
+  constexpr int NTWC = OLD ? M : OLDS ? H : 1;
   __shared__ float2 lds[LDS2];
-  __shared__ float2 tws[M];
-  __shared__ float2 twc[M];
-  __shared__ int4 srow_l[STAGE ? M : 1];
-  __shared__ float sval_l[NNZ];
+  __shared__ float2 tws[OLD ? M : 1];
+  __shared__ float2 twc[NTWC];
   const size_t zo = (size_t)blockIdx.z * zs;
   ctl = zsh(ctl, zo);
   const CtlHead hd = ctl_head(ctl);
   float* eout = vol_out(ep.out, hd, zo);
   const float* eref = vol_in(ep.ref, hd, zo);
   if (gated_off(hd, gate)) return;
-  zsh_tables(S, zo);
+  S.rows = zsh(S.rows, zo);
   spec = zsh(spec, zo);
-  tw = zsh(tw, zo);
-  twcg = zsh(twcg, zo);
+  zsh_tw(tt, zo);
   ep.partials = zsh(ep.partials, zo);
   const int tid = threadIdx.x;
   const int col0 = xcd_block(blockIdx.x, gridDim.x) * J;
-  // tables and the block's planes: one round trip
-  if constexpr (STAGE)
-    copy_together(tid, table_copy<NT, M>(tws, tw), table_copy<NT, M>(twc, twcg),
-                  table_copy<NT, M>(srow_l, S.rows), table_copy<NT, NNZ>(sval_l, S.rvals),
-                  planes_copy<J, NT, H>(lds, spec, nn, col0));
-  else
-    copy_together(tid, table_copy<NT, M>(tws, tw), table_copy<NT, M>(twc, twcg),
-                  planes_copy<J, NT, H>(lds, spec, nn, col0));
-  const int4* srow = STAGE ? srow_l : S.rows;
-  const float* sval = STAGE ? sval_l : S.rvals;
-  __syncthreads();
-  // solve phase: packed real inverse of length m (as k_tinv_solve)
   const bool sact = tid < J * GS;
   const int bs = tid / GS, ss = tid % GS;
+  // tables and the block's planes: one round trip
+  if constexpr (OLD)
+    copy_together(tid, table_copy<NT, M>(tws, tt.tw), table_copy<NT, NTWC>(twc, tt.twc),
+                  tangle_copy<J, NT, LOGH, 2>(lds, spec, tt.tw, nn, col0));
+  else if constexpr (OLDS)
+    copy_together(tid, table_copy<NT, NTWC>(twc, tt.twc),
+                  tangle_copy<J, NT, LOGH, 2>(lds, spec, tt.tw, nn, col0));
+  else
+    copy_together(tid, tangle_copy<J, NT, LOGH, 2>(lds, spec, tt.tw, nn, col0));
+  FftTw<LOGH> tw;
+  tw.load_b(tt.fb + FftCol<LOGM>::TB, ss);
+  tw.load_a(tt.fa + FftCol<LOGM>::TA, ss);
+  __syncthreads();
+  // solve phase: packed real inverse of length m (as k_tinv_solve)
   float2 y[ES];
-  if (sact) {
-#pragma unroll
-    for (int r = 0; r < ES; ++r) {
-      const int k = brev(GS * r + ss, LOGH);
-      float2 Xk = lds[stg<J>(k, bs)];
-      float2 Xm = lds[stg<J>((H - k) & (H - 1), bs)];
-      if (k == 0) {
-        Xm = make_float2(Xk.y, 0.f);
-        Xk.y = 0.f;
-      }
-      const float2 e = make_float2(0.5f * (Xk.x + Xm.x), 0.5f * (Xk.y - Xm.y));
-      const float2 o = make_float2(0.5f * (Xk.x - Xm.x), 0.5f * (Xk.y + Xm.y));
-      const float2 wo = cmulc(o, tws[2 * k]);
-      y[r] = make_float2(e.x - wo.y, e.y + wo.x);
-    }
-  }
+  if (sact) stage_get<LOGH, J>(lds, y, bs, ss);
   __syncthreads();                                 // staging consumed: the columns' LDS is reused
   double acc = 0.0;
   if (sact) {
-    dit_xlane<GS, ES>(y, ss, twc);
-    dit_inlane<GS, ES, ES / 2>(y, ss, twc);
     const int col = col0 + bs;
     float2* out2 = reinterpret_cast<float2*>(eout) + (size_t)col * H;
     // the reference is read unconditionally (the output column stands in
@@ -1768,6 +1796,7 @@ k_tinv_solve_fwd(float2* __restrict__ spec, int nn, ResampleTables S,
     const bool hr = eref != nullptr;
     const float2* ref2 = reinterpret_cast<const float2*>(hr ? eref : eout) + (size_t)col * H;
     float2* xf2 = lds + bs * ZS;                   // the column's real samples, as pairs
+    col_transform_inv<LOGH, false, 2>(y, xf2, tw, tws, twc, ss);
     float2 rv[ES];
 #pragma unroll
     for (int r = 0; r < ES; ++r) rv[r] = ref2[GS * r + ss];
@@ -1793,7 +1822,7 @@ k_tinv_solve_fwd(float2* __restrict__ spec, int nn, ResampleTables S,
   float xv[E];
 #pragma unroll
   for (int r = 0; r < E; ++r) xv[r] = xf[G * r + s];
-  tfwd_conv_from_lds<LOGM, PK>(lds, tws, twc, srow, sval, xv, tid, col0, spec, nn);
+  tfwd_conv_from_lds<LOGM>(lds, tt, tws, twc, S.rows, xv, tid, col0, spec, nn);
 }
 
 // exponentials staged in LDS by the H^ setup (2m <= this; 32 KB at most)
@@ -1916,6 +1945,28 @@ k_build_hq(float2* __restrict__ hq, int m, const int* __restrict__ dq,
 // ---------------------------------------------------------------------------
 // blocks of the t passes (their partial sums are indexed by block)
 int conv_blocks(int logn, int logm) { return (1 << (2 * logn)) / t_columns(logm); }
+// tables of the passes' lane twiddles (fft_column.h) for a time axis of 2^logm
+// bins: the convolution's transform, then the solve's
+void column_twiddles(int logm, std::vector<float2>& fa, std::vector<float2>& fb) {
+  const double PI = 3.14159265358979323846;
+  fa.clear();
+  fb.clear();
+  auto w = [&](double num, double den) {
+    return make_float2((float)cos(-2.0 * PI * num / den), (float)sin(-2.0 * PI * num / den));
+  };
+  for (int logf : {logm, logm - 1}) {
+    if (logf < 8 || logf > 10) continue;
+    const int F = 1 << logf, E = F / 64, low = E == 8 ? 7 : E == 4 ? 15 : 3;
+    for (int k = 1; k < E; ++k)
+      for (int l = 0; l < 64; ++l) {
+        fa.push_back(w((double)l * k, F));
+        fb.push_back(w((double)(l & low) * k, 64));
+      }
+    if (E == 4)
+      for (int j = 0; j < 16; ++j) fb.push_back(w(j, 16));
+  }
+}
+
 int solve_blocks(int logn, int logm) { return (1 << (2 * logn)) / t_columns(logm - 1); }
 int fused_solve_blocks(int logn, int logm) { return conv_blocks(logn, logm); }
 
@@ -1981,28 +2032,27 @@ static hipError_t conv_impl(const Tables& tb, const ConvSrc& src, float2* spec, 
                             int epi, const ConvEpi& ep, const DevCtl* ctl, const Batch& bt,
                             hipStream_t st, Prof* prof, bool tfwd_done, const RhsSrc* rhs_next) {
   constexpr int N = 1 << LOGN, M = 1 << LOGM, NN = N * N;
-  // the plane kernels take the real planes kt = 0, m packed in one (block 0)
-  constexpr bool PK = true;
+  const TwTabs tt{tb.tw_t, tb.twc_t, tb.fa, tb.fb};
   using TG = TGeo<LOGM>;
   const int nb = NN / TG::J;
   const int nz = bt.nz, g = bt.gate;
   const size_t zs = bt.zs, hzs = bt.hq_shared ? 0 : zs;
   if (!tfwd_done)
     CNLOS_TIMED(prof, KK_T_FWD_CONV, st,
-                hipLaunchKernelGGL((k_tfwd_conv<LOGM, PK>), dim3(nb, 1, nz), dim3(TG::NT), 0, st,
-                                   src, tb.S, tb.tw_t, tb.twc_t, spec, NN, ctl, zs, g));
+                hipLaunchKernelGGL((k_tfwd_conv<LOGM>), dim3(nb, 1, nz), dim3(TG::NT), 0, st,
+                                   src, tb.S, tt, spec, NN, ctl, zs, g));
   CNLOS_TIMED(prof, KK_PLANE_CONV, st, plane_conv<LOGN>(adjoint, M, tb, spec, ctl, zs, hzs, g, nz, st));
   const float scale = (float)(1.0 / (4.0 * (double)NN * (double)M));
   if (rhs_next) {
     if (epi == EPI_FWD_DUAL)
       CNLOS_TIMED(prof, KK_T_INV_CONV, st,
-                  hipLaunchKernelGGL((k_tinv_conv_rhs<LOGM, PK, EPI_FWD_DUAL>), dim3(nb, 1, nz),
-                                     dim3(TG::NT), 0, st, spec, NN, tb.S, tb.tw_t, tb.twc_t, ep,
+                  hipLaunchKernelGGL((k_tinv_conv_rhs<LOGM, EPI_FWD_DUAL>), dim3(nb, 1, nz),
+                                     dim3(TG::NT), 0, st, spec, NN, tb.S, tt, ep,
                                      scale, *rhs_next, const_cast<DevCtl*>(ctl), zs, g));
     else if (epi == EPI_PLAIN)
       CNLOS_TIMED(prof, KK_T_INV_CONV, st,
-                  hipLaunchKernelGGL((k_tinv_conv_rhs<LOGM, PK, EPI_PLAIN>), dim3(nb, 1, nz),
-                                     dim3(TG::NT), 0, st, spec, NN, tb.S, tb.tw_t, tb.twc_t, ep,
+                  hipLaunchKernelGGL((k_tinv_conv_rhs<LOGM, EPI_PLAIN>), dim3(nb, 1, nz),
+                                     dim3(TG::NT), 0, st, spec, NN, tb.S, tt, ep,
                                      scale, *rhs_next, const_cast<DevCtl*>(ctl), zs, g));
     else
       return hipErrorInvalidValue;
@@ -2010,8 +2060,8 @@ static hipError_t conv_impl(const Tables& tb, const ConvSrc& src, float2* spec, 
   }
 #define CNLOS_TINV(E)                                                                         \
   CNLOS_TIMED(prof, KK_T_INV_CONV, st,                                                        \
-              hipLaunchKernelGGL((k_tinv_conv<LOGM, E, PK>), dim3(nb, 1, nz), dim3(TG::NT), 0, \
-                                 st, spec, NN, tb.S, tb.tw_t, tb.twc_t, ep, scale, ctl, zs, g))
+              hipLaunchKernelGGL((k_tinv_conv<LOGM, E>), dim3(nb, 1, nz), dim3(TG::NT), 0, \
+                                 st, spec, NN, tb.S, tt, ep, scale, ctl, zs, g))
   switch (epi) {
     case EPI_PLAIN: CNLOS_TINV(EPI_PLAIN); break;
     case EPI_FWD_OBJ: CNLOS_TINV(EPI_FWD_OBJ); break;
@@ -2033,22 +2083,23 @@ static hipError_t solve_impl(const Tables& tb, const float* rhs, const RhsSrc& r
   const int nz = bt.nz, g = bt.gate;
   const size_t zs = bt.zs;
   DevCtl* c = const_cast<DevCtl*>(ctl);
+  const TwTabs tt{tb.tw_t, tb.twc_t, tb.fa, tb.fb};
   if (!tfwd_done) {
     switch (rs.mode) {
       case RHS_U:
         CNLOS_TIMED(prof, KK_T_FWD_SOLVE, st,
                     hipLaunchKernelGGL((k_tfwd_solve<LOGM, RHS_U>), dim3(nb, 1, nz), dim3(TG::NT), 0,
-                                       st, rhs, rs, tb.tw_t, tb.twc_t, spec, NN, c, zs, g));
+                                       st, rhs, rs, tt, spec, NN, c, zs, g));
         break;
       case RHS_TAU:
         CNLOS_TIMED(prof, KK_T_FWD_SOLVE, st,
                     hipLaunchKernelGGL((k_tfwd_solve<LOGM, RHS_TAU>), dim3(nb, 1, nz), dim3(TG::NT), 0,
-                                       st, rhs, rs, tb.tw_t, tb.twc_t, spec, NN, c, zs, g));
+                                       st, rhs, rs, tt, spec, NN, c, zs, g));
         break;
       default:
         CNLOS_TIMED(prof, KK_T_FWD_SOLVE, st,
                     hipLaunchKernelGGL((k_tfwd_solve<LOGM, RHS_LOAD>), dim3(nb, 1, nz), dim3(TG::NT),
-                                       0, st, rhs, rs, tb.tw_t, tb.twc_t, spec, NN, c, zs, g));
+                                       0, st, rhs, rs, tt, spec, NN, c, zs, g));
         break;
     }
   }
@@ -2058,15 +2109,14 @@ static hipError_t solve_impl(const Tables& tb, const float* rhs, const RhsSrc& r
   if (fwd_next) {
     // with the forward t pass of the convolution of the result
     using TC = TGeo<LOGM>;
-    constexpr bool PK = true;
     CNLOS_TIMED(prof, KK_T_INV_SOLVE, st,
-                hipLaunchKernelGGL((k_tinv_solve_fwd<LOGM, PK>), dim3(NN / TC::J, 1, nz),
-                                   dim3(TC::NT), 0, st, spec, NN, tb.S, tb.tw_t, tb.twc_t, ep,
+                hipLaunchKernelGGL((k_tinv_solve_fwd<LOGM>), dim3(NN / TC::J, 1, nz),
+                                   dim3(TC::NT), 0, st, spec, NN, tb.S, tt, ep,
                                    scale, ctl, zs, g));
   } else {
     CNLOS_TIMED(prof, KK_T_INV_SOLVE, st,
                 hipLaunchKernelGGL(k_tinv_solve<LOGM>, dim3(nb, 1, nz), dim3(TG::NT), 0, st, spec,
-                                   NN, tb.tw_t, tb.twc_t, ep, scale, ctl, zs, g));
+                                   NN, tt, ep, scale, ctl, zs, g));
   }
   return hipGetLastError();
 }
