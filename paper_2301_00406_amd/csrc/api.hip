@@ -203,6 +203,7 @@ struct cnlos_problem {
   bool in_batch = false;      // owned by a cnlos_batch
   size_t carve_bytes = 0;
   int iter_host = 0;
+  double L0_obj = 1.0, L0_dual = 1.0;   // step constants of the initial state
   DevCtl* ctl = nullptr;
   DevCtl* ctl_host = nullptr;   // pinned mirror
   double* partials = nullptr;
@@ -585,49 +586,42 @@ cnlos_status power_estimate(cnlos_problem* p, bool masked, double* est) {
   return power_estimate(p, kSingle, &p, masked, est);
 }
 
-cnlos_status reset_state(cnlos_problem* p) {
+// The initial ADMM state (create: tau0 too).  Asynchronous: one launch.
+cnlos_status reset_state(cnlos_problem* p, bool create = false) {
   const size_t V = p->V;
-  float* zero[] = {p->U[0], p->U[1], p->UB[0], p->UB[1], p->AU[0], p->AU[1], p->AU[2], p->gf};
-  for (float* z : zero) HIPCHK(launch_fill(z, V, 0.f, p->st));
-  HIPCHK(launch_fill(p->lam, 3 * V, 0.f, p->st));
-  HIPCHK(launch_fill(p->phi, V, (float)phi_at_zero(phi_args(p, 1, false)), p->st));
+  ResetArgs a{};
+  a.L0_obj = p->L0_obj;
+  a.L0_dual = p->L0_dual;
+  a.stage1_end = p->cfg.model == CNLOS_MODEL_DUAL ? p->cfg.init_iters : 0x7fffffff;
+  // volumes of one value that follow one another in the workspace are one segment
+  auto fill = [&](float* q, size_t n, float val) {
+    if (a.nseg > 0) {
+      ResetArgs::Seg& last = a.seg[a.nseg - 1];
+      if (last.p + last.n == q && last.val == val) {
+        last.n += n;
+        return;
+      }
+    }
+    a.seg[a.nseg++] = {q, n, val};
+  };
+  std::vector<std::pair<float*, size_t>> zero;
+  if (create) zero.push_back({p->tau0, V});
+  for (float* z : {p->U[0], p->U[1], p->UB[0], p->UB[1]}) zero.push_back({z, V});
+  zero.push_back({p->lam, 3 * V});
+  for (float* z : {p->AU[0], p->AU[1], p->AU[2], p->gf}) zero.push_back({z, V});
   if (p->cfg.model == CNLOS_MODEL_DUAL) {
-    float* zd[] = {p->T[0], p->T[1], p->TB[0], p->TB[1], p->lam3};
-    for (float* z : zd) HIPCHK(launch_fill(z, V, 0.f, p->st));
-    HIPCHK(launch_fill(p->lam2, 3 * V, 0.f, p->st));
-    HIPCHK(launch_fill(p->phi_tau, V, (float)phi_at_zero(phi_args(p, 2, true)), p->st));
+    for (float* z : {p->T[0], p->T[1], p->TB[0], p->TB[1]}) zero.push_back({z, V});
+    zero.push_back({p->lam2, 3 * V});
+    zero.push_back({p->lam3, V});
   }
-  cnlos_status s = ctl_pull(p);
-  if (s != CNLOS_OK) return s;
-  DevCtl& c = *p->ctl_host;
-  c.L = c.L0_obj;
-  c.t = 1.0;
-  c.beta = 0.0;
-  c.energy_prev = NAN;
-  c.halt = 0;
-  c.reason = HR_NONE;
-  c.iter = 0;
-  c.trials = 0;
-  c.bt_rejects = 0;
-  c.stage = 1;
-  c.log_count = 0;
-  c.target = 0;
-  c.reject = 0;
-  c.stage1_end = p->cfg.model == CNLOS_MODEL_DUAL ? p->cfg.init_iters : 0x7fffffff;
-  c.slot[R_U_CUR] = 0;
-  c.slot[R_U_TR] = 1;
-  c.slot[R_AU_CUR] = 0;
-  c.slot[R_AU_PREV] = 2;
-  c.slot[R_AU_TR] = 1;
-  c.slot[R_T_CUR] = 0;
-  c.slot[R_T_TR] = 1;
-  c.slot[R_UB_CUR] = 0;
-  c.slot[R_UB_NEW] = 1;
-  c.slot[R_TB_CUR] = 0;
-  c.slot[R_TB_NEW] = 1;
-  c.slot_pad = 0;
+  for (const auto& z : zero) fill(z.first, z.second, 0.f);
+  fill(p->phi, V, (float)phi_at_zero(phi_args(p, 1, false)));
+  if (p->cfg.model == CNLOS_MODEL_DUAL)
+    fill(p->phi_tau, V, (float)phi_at_zero(phi_args(p, 2, true)));
+  HIPCHK(launch_reset(a, p->ctl, p->st));
+  reset_ctl(*p->ctl_host, a);
   p->iter_host = 0;
-  return ctl_push(p);
+  return CNLOS_OK;
 }
 
 // Sequences of one iteration slot.  Every kernel carries a phase gate, so a
@@ -966,7 +960,14 @@ cnlos_status run_groups(std::vector<Group>& gs, int32_t iters, std::vector<cnlos
     cnlos_status s = group_start(gs[gi], runs[gi], iters);
     if (s != CNLOS_OK) return s;
   }
-  int batch = 2;
+  // Slots enqueued per wait.  Runs that may stop early start with few, so that
+  // they do not enqueue many slots past their end; without a stopping rule every
+  // slot is needed (a rejection only adds one), so the first wait comes after 64
+  // (16 iterations of 64x64x512 waited five times with 2, 4, 8, ...).
+  bool may_stop = false;
+  for (const Group& g : gs)
+    for (const cnlos_problem* m : g.mem) may_stop = may_stop || m->cfg.eps_stop > 0.0;
+  int batch = may_stop ? 2 : 64;
   for (;;) {
     bool any = false;
     std::vector<char> busy(gs.size(), 0);
@@ -1348,14 +1349,11 @@ cnlos_status finish_create(cnlos_problem* p, double est_masked, double est_unmas
   const double L0o = cfg->L0 > 0.0 ? cfg->L0 : 2.0 * est_masked;
   const double L0d = cfg->model != CNLOS_MODEL_DUAL ? L0o
                      : (cfg->L0_dual > 0.0 ? cfg->L0_dual : 2.0 * est_unmasked);
-  cnlos_status s = ctl_pull(p);
+  p->L0_obj = L0o;
+  p->L0_dual = L0d;
+  cnlos_status s = reset_state(p, true);
   if (s != CNLOS_OK) return s;
-  p->ctl_host->L0_obj = L0o;
-  p->ctl_host->L0_dual = L0d;
-  s = ctl_push(p);
-  if (s != CNLOS_OK) return s;
-  HIPCHK(launch_fill(p->tau0, p->V, 0.f, p->st));
-  return reset_state(p);
+  return ctl_pull(p);   // creation waits for the stream
 }
 
 }  // namespace
@@ -1601,6 +1599,7 @@ cnlos_status cnlos_tune(cnlos_problem* p, cnlos_plan* out) {
   // the timing runs used the A u buffers: the solver starts afresh
   if (p->cfg.model != CNLOS_MODEL_OPERATOR) {
     cnlos_status s = reset_state(p);
+    if (s == CNLOS_OK) s = ctl_pull(p);
     if (s != CNLOS_OK) return s;
   }
   if (out) plan_out(best, p->logn, true, conv_us, solve_us, out);

@@ -395,6 +395,50 @@ hipError_t launch_transition(int logn, int logm, DevCtl* ctl, Vol u, Vol ubar,
                              float* const* zero_fields, const size_t* zero_counts, int nzero,
                              const Batch& bt, hipStream_t st);
 hipError_t launch_fill(float* x, size_t n, float val, hipStream_t st);
+// the ADMM state of a problem as at its creation, in one launch: volumes filled
+// by segments (16-byte aligned, multiples of 4 floats), and the controller
+struct ResetArgs {
+  struct Seg {
+    float* p;
+    size_t n;
+    float val;
+  } seg[18];              // every volume group on its own, at most
+  int nseg;
+  double L0_obj, L0_dual;
+  int stage1_end;
+};
+// the controller's part (also on the host's mirror)
+__host__ __device__ inline void reset_ctl(DevCtl& c, const ResetArgs& a) {
+  c.L0_obj = a.L0_obj;
+  c.L0_dual = a.L0_dual;
+  c.L = a.L0_obj;
+  c.t = 1.0;
+  c.beta = 0.0;
+  c.energy_prev = __builtin_nan("");
+  c.halt = 0;
+  c.reason = HR_NONE;
+  c.iter = 0;
+  c.trials = 0;
+  c.bt_rejects = 0;
+  c.stage = 1;
+  c.log_count = 0;
+  c.target = 0;
+  c.reject = 0;
+  c.stage1_end = a.stage1_end;
+  c.slot[R_U_CUR] = 0;
+  c.slot[R_U_TR] = 1;
+  c.slot[R_AU_CUR] = 0;
+  c.slot[R_AU_PREV] = 2;
+  c.slot[R_AU_TR] = 1;
+  c.slot[R_T_CUR] = 0;
+  c.slot[R_T_TR] = 1;
+  c.slot[R_UB_CUR] = 0;
+  c.slot[R_UB_NEW] = 1;
+  c.slot[R_TB_CUR] = 0;
+  c.slot[R_TB_NEW] = 1;
+  c.slot_pad = 0;
+}
+hipError_t launch_reset(const ResetArgs& a, DevCtl* ctl, hipStream_t st);
 hipError_t launch_copy(float* dst, const float* src, size_t n, hipStream_t st);
 hipError_t launch_phi_of_u(int logn, int logm, const float* u, float* phi, const PhiArgs& pa,
                            hipStream_t st);
