@@ -96,22 +96,23 @@ __device__ __forceinline__ double nc_in_branch(double z) {
 constexpr double kNearBin = 1e-8;
 
 // A path from its squared detector distance d2 = (ex^2 + ey^2) + z^2 and the
-// voxel's illumination distance di: the bin, and 1 / d_d^2.
+// voxel's illumination distance less half a bin, dh = d_i - c dt / 2: the bin
+// (not limited to the window), and 1 / d_d^2.
 struct NcFast {
   int bin;
   bool near;    // decide the bin with nc_path
   double r2;
 };
-__device__ __forceinline__ NcFast nc_fast(double d2, double di, double inv_cdt, int m) {
+__device__ __forceinline__ NcFast nc_fast(double d2, double dh, double inv_cdt) {
   const double r = nc_rsqrt(d2);
-  const double q = fma(d2, r, di) * inv_cdt;
-  // the nearest whole number through the addition of 1.5 2^52 (q < 2^30, see
-  // nc_in_range): its low word is the integer
-  const double t = q + 6755399441055744.0;
-  const double off = q - (t - 6755399441055744.0);      // [-1/2, 1/2], exact
+  const double len = fma(d2, r, dh);
+  // the whole number nearest to the quotient less 1/2, through the addition of
+  // 1.5 2^52 (the quotient is below 2^30, see nc_in_range): its low word is the bin
+  const double t = fma(len, inv_cdt, 6755399441055744.0);
+  const double off = fma(len, inv_cdt, 6755399441055744.0 - t);   // [-1/2, 1/2]
   NcFast f;
-  f.bin = min(__double2loint(t) + (__double2hiint(off) >> 31), m);
-  f.near = fabs(off) < kNearBin;
+  f.bin = __double2loint(t);
+  f.near = fabs(off) > 0.5 - kNearBin;
   f.r2 = r * r;
   return f;
 }
@@ -128,9 +129,20 @@ __device__ __forceinline__ void nc_bin_add(double* h, double v) {
 __host__ __device__ constexpr int nc_place(int b) { return b + (b >> 3); }
 constexpr int kNcRow = 72;   // LDS row of u by [j][lane] (the pad spreads the transposed stores)
 
+// Steps of 64 depths that a column needs: with more depth every path to the
+// detectors leaves the window.  d_i + d_d = P = m c dt puts d_i at
+// (P + (lat_i - lat_d) / P) / 2; two depths more than that are kept.
+__device__ __forceinline__ int nc_steps(const NcGeo& g, double lat_i, double lat_d, int S) {
+  const double P = g.m * g.cdt, di = 0.5 * (P + (lat_i - lat_d) / P);
+  const double z2 = di > 0.0 && di < P ? fmax(di * di - lat_i, 0.0) : 0.0;
+  const double k = fmin(sqrt(z2) * (g.m / g.range), (double)g.m);
+  return min(S, ((int)k + 2 + 63) >> 6);
+}
+
 // tau[det][b] = sum over voxels with path bin b of w u.  One block per D
 // detectors; wave w takes the columns w, w + W, ... in order, and lane l
-// the S = ceil(m / 64) consecutive depths from S l on, so that
+// the s consecutive depths from s l on (s = ceil(m / 64), or fewer where the
+// deeper paths leave the window), so that
 //   - the illumination distance and u of a voxel serve D detectors;
 //   - a lane's bins never decrease from one depth to the next (the path grows
 //     with the depth): a lane sums a run of equal bins in a register and adds
@@ -139,38 +151,30 @@ constexpr int kNcRow = 72;   // LDS row of u by [j][lane] (the pad spreads the t
 //     step j, a lane above it whose bin is the same has not reached a new bin
 //     either, since all its depths are larger.  Only the runs left at the end
 //     of a column can meet; they are added in lane order.
+// Depths from m on need no test: their paths are longer than the window.
 // A column's u is read coalesced (SM >= S loads, the next column's while this
 // one is summed) and handed to the lanes through LDS: read in place, at a
 // stride of S floats, the columns of a CU's waves overrun its L1 (64x64x512,
 // one detector per block: 15.0 against 13.8 ms).
 // Consecutive depths in consecutive lanes, with a segmented scan over equal
 // bins per 64 paths (18 lane exchanges through the LDS pipe), and the plain path
-// arithmetic took 42.6 ms at 64x64x512 and 1.59 ms at 32x32x256; now 11.8 and
-// 0.44 ms, issuing vector instructions in about three quarters of the cycles.
+// arithmetic took 42.6 ms at 64x64x512 and 1.59 ms at 32x32x256; now 10.5
+// and 0.39 ms, issuing vector instructions in about three quarters of the cycles.
+// Leaving out the depths beyond the window is worth 229 -> 120 us where paths are
+// long for it (24x24x224, 1.5 m wall, 12 ps bins) and nothing where all fit.
 template <int D, bool LIT, int SM>
 __global__ void __launch_bounds__(64 * kNcMaxWaves)
 k_nc_forward(NcGeo g, const float* __restrict__ u, float* __restrict__ tau) {
-  // histograms [W][D][M], z [S][64] by [j][lane], then u [W][S][kNcRow]
+  // histograms [W][M][D], then u [W][S + 1][kNcRow]; the last row is read ahead only
   extern __shared__ double nc_lds[];
   __shared__ double xs[kNcMaxGridDev];
   const int m = g.m, n = g.n, S = (m + 63) >> 6, nt = blockDim.x, W = nt >> 6;
   const int M = nc_place(m);                   // places of one histogram
-  double* zs = nc_lds + W * D * M;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   for (int b = threadIdx.x; b < W * D * M; b += nt) nc_lds[b] = 0.0;
   for (int i = threadIdx.x; i < n; i += nt) xs[i] = nc_lateral(g, i);
-  for (int i = threadIdx.x; i < 64 * S; i += nt) zs[i] = nc_depth(g, S * (i & 63) + (i >> 6));
   __syncthreads();
-  // this lane's depths 64 i + lane in the order they are read from memory, and
-  // their places by [j][lane]: k = S l + j (k S' >> 16 = k / S for k < 1024)
-  float* ub = reinterpret_cast<float*>(zs + 64 * S) + wv * S * kNcRow;
-  const int inv_s = (65536 + S - 1) / S;
-  int place[SM];
-#pragma unroll
-  for (int i = 0; i < SM; ++i) {
-    const int k = min(64 * i + lane, 64 * S - 1), l = (k * inv_s) >> 16;
-    place[i] = (k - l * S) * kNcRow + l;
-  }
+  float* ub = reinterpret_cast<float*>(nc_lds + W * D * M) + wv * (S + 1) * kNcRow;
   float nu[SM];
   auto load_column = [&](int col) {
     const float* uc = u + (size_t)col * m;
@@ -185,9 +189,35 @@ k_nc_forward(NcGeo g, const float* __restrict__ u, float* __restrict__ tau) {
     xd[d] = xs[det / n];
     yd[d] = xs[det % n];
   }
-  const double inv_cdt = 1.0 / g.cdt;
+  const double inv_cdt = 1.0 / g.cdt, dz = g.range / m;
   double* h = nc_lds + wv * D * M;
-  for (int col = wv; col < n * n; col += W) {
+  int place[SM];
+  int s = 0, steps = S, c = 0;
+  for (int col = wv; col < n * n; col += W, ++c) {
+    if ((c & 63) == 0 && !g.plain) {
+      // lane l: the steps of the wave's l-th column from here on
+      const int cl = min(col + lane * W, n * n - 1);
+      const double xv = xs[cl / n], yv = xs[cl % n];
+      const double ex = xv - g.ix, ey = yv - g.iy;
+      steps = 0;
+#pragma unroll
+      for (int d = 0; d < D; ++d) {
+        const double fx = xv - xd[d], fy = yv - yd[d];
+        steps = max(steps, nc_steps(g, ex * ex + ey * ey, fx * fx + fy * fy, S));
+      }
+    }
+    const int sc = __builtin_amdgcn_readlane(steps, c & 63);
+    if (sc != s) {
+      // this lane's depths 64 i + lane in the order they are read from memory,
+      // and their places by [j][lane]: k = s l + j (k s' >> 16 = k / s for k < 1024)
+      s = sc;
+      const int inv_s = (65536 + s - 1) / s;
+#pragma unroll
+      for (int i = 0; i < SM; ++i) {
+        const int k = min(64 * i + lane, 64 * s - 1), l = (k * inv_s) >> 16;
+        place[i] = (k - l * s) * kNcRow + l;
+      }
+    }
     const double xv = xs[col / n], yv = xs[col % n];
     double lat_i, lat_d[D];
     {
@@ -203,7 +233,7 @@ k_nc_forward(NcGeo g, const float* __restrict__ u, float* __restrict__ tau) {
     // only this wave's lanes touch ub, and a wave's LDS accesses are in order
 #pragma unroll
     for (int i = 0; i < SM; ++i)
-      if (i < S) ub[place[i]] = nu[i];
+      if (i < s) ub[place[i]] = nu[i];
     if (col + W < n * n) load_column(col + W);
     __builtin_amdgcn_wave_barrier();
     int cur[D];
@@ -213,55 +243,46 @@ k_nc_forward(NcGeo g, const float* __restrict__ u, float* __restrict__ tau) {
       cur[d] = m;
       acc[d] = 0.0;
     }
-    double z = zs[lane];
+    double kd = s * lane + 0.5;
     float uf = ub[lane];
-    for (int j = 0; j < S; ++j) {
-      const int k = S * lane + j;
-      const bool in = k < m;
-      // the next step's operands are read before this one's arithmetic
-      const int jn = min(j + 1, S - 1);
-      const double zn = zs[64 * jn + lane];
-      const float un = ub[jn * kNcRow + lane];
-      const double uv = (double)uf;
-      double zz, d2i;
-      {
-#pragma clang fp contract(off)
-        zz = z * z;
-        d2i = lat_i + zz;
-      }
-      const double ri = nc_rsqrt(d2i);
-      const double di = d2i * ri;
-      const double wu = LIT ? uv * (ri * ri) : uv;
+    for (int j = 0; j < s; ++j) {
+      // the next step's operand is read before this one's arithmetic
+      const float un = ub[(j + 1) * kNcRow + lane];
+      const double uv = (double)uf, z = kd * dz, zz = z * z;
+      const double d2i = lat_i + zz, ri = nc_rsqrt(d2i);
+      const double dh = fma(d2i, ri, -0.5 * g.cdt);
+      double wu = LIT ? uv * (ri * ri) : uv;
       NcFast f[D];
-      double val[D];
       bool near = g.plain != 0;
 #pragma unroll
       for (int d = 0; d < D; ++d) {
-        f[d] = nc_fast(lat_d[d] + zz, di, inv_cdt, m);
+        f[d] = nc_fast(lat_d[d] + zz, dh, inv_cdt);
         near |= f[d].near;
-        val[d] = LIT ? wu * f[d].r2 : wu;
       }
       if (near) {
-        const double zp = nc_in_branch(z);
+        const int k = s * lane + j;
+        const double zp = nc_in_branch(nc_depth(g, k));
         const double dp = nc_illum_dist(g, xv, yv, zp);
+        if (g.plain) wu = uv;
 #pragma unroll
         for (int d = 0; d < D; ++d) {
           const NcPath r = nc_path(g, xd[d], yd[d], xv, yv, zp, dp);
-          f[d].bin = r.bin;
-          if (g.plain) val[d] = r.w * uv;
+          f[d].bin = k < m ? r.bin : m;
+          if (g.plain) f[d].r2 = r.w;
         }
       }
 #pragma unroll
       for (int d = 0; d < D; ++d) {
-        const int bin = in ? f[d].bin : m;
-        if (bin != cur[d]) {
-          if (cur[d] < m) nc_bin_add(h + d * M + nc_place(cur[d]), acc[d]);
-          cur[d] = bin;
+        if (j == 0) cur[d] = f[d].bin;
+        // a lane whose bin has left the window has nothing more to add
+        if (f[d].bin != cur[d] && cur[d] < m) {
+          nc_bin_add(h + nc_place(cur[d]) * D + d, acc[d]);
+          cur[d] = f[d].bin;
           acc[d] = 0.0;
         }
-        acc[d] += val[d];
+        acc[d] = LIT ? fma(wu, f[d].r2, acc[d]) : acc[d] + wu;
       }
-      z = zn;
+      kd += 1.0;
       uf = un;
     }
     __builtin_amdgcn_wave_barrier();
@@ -273,7 +294,7 @@ k_nc_forward(NcGeo g, const float* __restrict__ u, float* __restrict__ tau) {
       unsigned long long todo = __ballot(cur[d] < m);
       while (todo) {                             // at most 64 rounds: `same` loses a lane each
         const unsigned long long now = todo & ~same;
-        if ((now >> lane) & 1) nc_bin_add(h + d * M + nc_place(cur[d]), acc[d]);
+        if ((now >> lane) & 1) nc_bin_add(h + nc_place(cur[d]) * D + d, acc[d]);
         todo &= same;
         same &= same << 1;
       }
@@ -285,9 +306,9 @@ k_nc_forward(NcGeo g, const float* __restrict__ u, float* __restrict__ tau) {
     const int det = blockIdx.x * D + d;
     if (det >= n * n) break;
     for (int b = threadIdx.x; b < m; b += nt) {
-      double s = 0.0;
-      for (int w = 0; w < W; ++w) s += nc_lds[(w * D + d) * M + nc_place(b)];
-      tau[(size_t)det * m + b] = (float)s;
+      double sum = 0.0;
+      for (int w = 0; w < W; ++w) sum += nc_lds[(w * M + nc_place(b)) * D + d];
+      tau[(size_t)det * m + b] = (float)sum;
     }
   }
 }
@@ -295,8 +316,9 @@ k_nc_forward(NcGeo g, const float* __restrict__ u, float* __restrict__ tau) {
 // u[p][q][k] = sum over detectors (in index order) of w tau[det][bin].  A wave
 // takes 64 depths of one column, so the squared lateral distances to the
 // detector rows and columns are tables in LDS that the wave reads as
-// broadcasts, and a path's squared distance is two additions (2.61 -> 1.24 ms
-// at 45x45x300, bound by FP64 issue).
+// broadcasts, and a path's squared distance is two additions.  Detectors beyond
+// the reach of the wave's shallowest depth are left out, row by row.  Bound by FP64
+// issue: 45x45x300 2.61 -> 1.09 ms, 24x24x224 with a 1.5 m wall 0.14 -> 0.075.
 constexpr int kNcTWaves = 4;
 template <bool LIT>
 __global__ void __launch_bounds__(64 * kNcTWaves)
@@ -308,13 +330,15 @@ k_nc_transpose(NcGeo g, const float* __restrict__ tau, float* __restrict__ u) {
   const int item = min((int)blockIdx.x * kNcTWaves + wv, items - 1);
   const int col = item / nchunk, k0 = (item - col * nchunk) * 64;
   const double xv = nc_lateral(g, col / n), yv = nc_lateral(g, col % n);
-  double* lx = nc_lds + wv * 2 * n;
+  double* lx = nc_lds + wv * (2 * n + 1);
   double* ly = lx + n;
-  for (int i = lane; i < n; i += 64) {
+  // one offset more, of a detector that no path reaches within the window
+  const double far = m * g.cdt;
+  for (int i = lane; i < n + 1; i += 64) {
 #pragma clang fp contract(off)
-    const double ex = xv - nc_lateral(g, i), ey = yv - nc_lateral(g, i);
-    lx[i] = ex * ex;
-    ly[i] = ey * ey;
+    const double x = nc_lateral(g, i), ex = xv - x, ey = yv - x;
+    if (i < n) lx[i] = ex * ex;
+    ly[i] = i < n ? ey * ey : far * far;
   }
   __syncthreads();
   const int k = min(k0 + lane, m - 1);
@@ -325,39 +349,56 @@ k_nc_transpose(NcGeo g, const float* __restrict__ tau, float* __restrict__ u) {
 #pragma clang fp contract(off)
     zz = z * z;
   }
-  const double inv_cdt = 1.0 / g.cdt;
+  const double inv_cdt = 1.0 / g.cdt, dh = di - 0.5 * g.cdt;
+  // squared lateral distance beyond which the paths of the first, shallowest
+  // depth leave the window, and so all the wave's do
+  const double z0 = nc_depth(g, k0), reach = far - nc_illum_dist(g, xv, yv, z0);
+  const double lat = (reach > 0.0 ? reach * reach - z0 * z0 : -1.0) + 1e-9 * far * far;
+  const double per = n / g.wall, jv = (yv / g.wall + 0.5) * n - 0.5;
   double acc = 0.0;
   for (int i = 0; i < n; ++i) {
     const double x2 = lx[i];
+    int ja = 0, jb = n;
+    if (!g.plain) {
+      // the detectors of the row within reach, and one on either side
+      const double rem = lat - x2, w = sqrt(fmax(rem, 0.0)) * per;
+      ja = max(0, (int)fmax(jv - w, 0.0) - 1);
+      jb = rem < 0.0 ? 0 : min(n, (int)fmin(jv + w, (double)n) + 2);
+    }
+    ja = __builtin_amdgcn_readfirstlane(ja);
+    jb = __builtin_amdgcn_readfirstlane(jb);
     // four detectors at a time: their loads are unconditional (bin clamped into
-    // the column, term masked) and issue together, and one branch serves the
+    // the column, value masked) and issue together, and one branch serves the
     // rare bins of all four
-    for (int j0 = 0; j0 < n; j0 += 4) {
+    for (int j0 = ja; j0 < jb; j0 += 4) {
       NcFast f[4];
-      double w[4];
+      const float* td[4];       // in scalar registers
       bool near = g.plain != 0;
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        f[q] = nc_fast((x2 + ly[min(j0 + q, n - 1)]) + zz, di, inv_cdt, m);
+        td[q] = tau + (size_t)__builtin_amdgcn_readfirstlane((i * n + min(j0 + q, n - 1)) * m);
+        f[q] = nc_fast((x2 + ly[min(j0 + q, n)]) + zz, dh, inv_cdt);
         near |= f[q].near;
-        w[q] = LIT ? f[q].r2 : 1.0;
       }
       if (near) {
         const double zp = nc_in_branch(z);
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const NcPath r = nc_path(g, nc_lateral(g, i), nc_lateral(g, min(j0 + q, n - 1)), xv, yv, zp, di);
-          f[q].bin = r.bin;
-          if (g.plain) w[q] = r.w;
+          f[q].bin = j0 + q < n ? r.bin : m;
+          if (g.plain) f[q].r2 = f[q].bin < m ? r.w : 0.0;
         }
       }
       float t[4];
 #pragma unroll
       for (int q = 0; q < 4; ++q)
-        t[q] = tau[(i * n + min(j0 + q, n - 1)) * m + min(f[q].bin, m - 1)];
+        t[q] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(td[q]) +
+                                               ((uint32_t)min(f[q].bin, m - 1) << 2));
 #pragma unroll
-      for (int q = 0; q < 4; ++q)
-        acc += (f[q].bin < m && j0 + q < n) ? w[q] * (double)t[q] : 0.0;
+      for (int q = 0; q < 4; ++q) {
+        const double tq = f[q].bin < m ? t[q] : 0.f;
+        acc = LIT ? fma(f[q].r2, tq, acc) : acc + tq;
+      }
     }
   }
   if (LIT && !g.plain) {
@@ -369,11 +410,11 @@ k_nc_transpose(NcGeo g, const float* __restrict__ tau, float* __restrict__ u) {
 
 }  // namespace
 
-// Histograms, depths and columns of the forward kernel: at most 60 KiB with the counts
+// Histograms and columns of the forward kernel: at most 58 KiB with the counts
 // of waves and detectors that launch_nc_forward takes.
 static size_t nc_forward_lds_bytes(int m, int d, int waves) {
   const size_t s = (m + 63) / 64;
-  return ((size_t)waves * d * nc_place(m) + 64 * s) * sizeof(double) + waves * s * kNcRow * sizeof(float);
+  return (size_t)waves * d * nc_place(m) * sizeof(double) + waves * (s + 1) * kNcRow * sizeof(float);
 }
 
 // Squared distances outside [1e-120, 1e120], and paths of 2^30 bins, are left
@@ -391,10 +432,11 @@ hipError_t launch_nc_forward(const NcGeo& g0, const float* u, float* tau, hipStr
   // histograms leave room for half the waves.  Measured, one against two
   // detectors: 24x24x224 237 / 263 us, 32x32x256 515 / 462, 45x45x300
   // 2284 / 1985, 64x64x512 13.8 / 12.4 ms, 40x40x1000 5.9 / 8.7 ms.  Eight waves
-  // while that leaves three blocks per CU, else four (64x64x512, two detectors:
-  // 15.5 ms with eight, 12.4 with four).
+  // while two blocks of them find room on a CU, with registers for both, else
+  // four: eight against four, 24x24x512 400 / 424 us, 24x24x560 583 / 476,
+  // 33x33x320 727 / 790, 64x64x512 (two detectors) 15.5 / 12.4 ms.
   const bool two = g.n >= 32 && g.m <= 512;
-  const int waves = 8 * (two ? 2 : 1) * nc_place(g.m) * 8 <= 48 * 1024 ? 8 : 4;
+  const int waves = nc_forward_lds_bytes(g.m, two ? 2 : 1, 8) <= 60 * 1024 ? 8 : 4;
   const int nd = g.n * g.n;
   const int S = (g.m + 63) / 64;
 #define CNLOS_NCF(D, LIT, SM)                                                              \
@@ -421,7 +463,7 @@ hipError_t launch_nc_transpose(const NcGeo& g0, const float* tau, float* u, hipS
   g.plain = nc_in_range(g) ? 0 : 1;
   const int items = g.n * g.n * ((g.m + 63) / 64);
   const dim3 grid((items + kNcTWaves - 1) / kNcTWaves), block(64 * kNcTWaves);
-  const size_t lds = (size_t)kNcTWaves * 2 * g.n * sizeof(double);
+  const size_t lds = (size_t)kNcTWaves * (2 * g.n + 1) * sizeof(double);
   if (g.literal) hipLaunchKernelGGL(k_nc_transpose<true>, grid, block, lds, st, g, tau, u);
   else hipLaunchKernelGGL(k_nc_transpose<false>, grid, block, lds, st, g, tau, u);
   return hipGetLastError();

@@ -196,3 +196,26 @@ def test_distances_beyond_the_fast_path(scale):
     ut = to_host(C.nc_apply_T(g, to_dev(torch, u)))
     assert rel_l2(tau, O.apply_nonconfocal(u, og, False)) <= TOL
     assert rel_l2(ut, O.apply_nonconfocal_T(u, og, False)) <= TOL
+
+
+# walls wide for the time window: most depths of a column, or all but the
+# shallowest, lie outside it, for some detectors and not for others; an
+# illumination point off the wall leaves columns without any path; the two wave
+# counts where the LDS of eight waves nears its limit
+@pytest.mark.parametrize("n,m,wall,dt,illum,literal", [
+    (12, 64, 3.0, 40.0, (0.0, 0.0), True), (13, 200, 2.0, 12.0, (0.9, -0.9), False),
+    (9, 300, 1.0, 20.0, (1.5, 0.0), True), (33, 70, 1.5, 30.0, (0.7, 0.2), True),
+    (8, 530, 2.5, 9.0, (0.1, 0.0), True), (8, 540, 2.5, 9.0, (0.1, 0.0), False)])
+def test_paths_beyond_the_window(n, m, wall, dt, illum, literal):
+    torch = need_gpu()
+    say(f"nonconfocal window n={n} m={m}")
+    g, og = _geoms(n, m, wall, dt, illum, literal)
+    u = f32(scenes.random_volume((n, n, m), 43 + n))
+    t = f32(scenes.random_signed((n, n, m), 47 + m))
+    tau = to_host(C.nc_apply(g, to_dev(torch, u)))
+    ut = to_host(C.nc_apply_T(g, to_dev(torch, t)))
+    ref, ref_t = O.apply_nonconfocal(u, og, literal), O.apply_nonconfocal_T(t, og, literal)
+    assert 0 < np.count_nonzero(ref_t) < 0.8 * ref_t.size
+    assert np.array_equal(tau != 0.0, ref != 0.0) and np.array_equal(ut != 0.0, ref_t != 0.0)
+    assert rel_l2(tau, ref) <= TOL and max_rel(tau, ref) <= TOL
+    assert rel_l2(ut, ref_t) <= TOL and max_rel(ut, ref_t) <= TOL
