@@ -1878,26 +1878,39 @@ __device__ __forceinline__ void hq_store(float2* __restrict__ Hk, int kx, int ky
 // c_0 = 1, c_d = 2.  One block per (kt, chunk of ky); FP64 accumulation; the
 // inner dy sum is staged in LDS.  Computed for kx, ky in [0, n] (the
 // quarter) and stored by hq_store.
+// cos(pi (n - k) d / n) = (-1)^d cos(pi k d / n): the sums over even and over
+// odd d give the frequencies k and n - k together, so a block takes KP pairs of
+// ky, and a thread R pairs at a time, which share the exponential and its
+// lookups (then one pair of kx and four ky, which share the cosine).  Bound by
+// its LDS reads: one frequency per sum and thread took 247 us at 64x64x512 and
+// 5.74 ms at 128x128x1024; now 74 us and 0.88 ms.
 // The kernel offsets dq (n <= 64) and, with ET, the exponential table
 // exp(-pi i j / m), j < 2m (dynamic LDS, 2m entries), are staged in LDS; 2m is
 // a power of two, so the phase index kt q mod 2m is a mask (kt q < 2^31 for
 // m <= 2^15).  Offsets outside the cone (dq < 0) enter with weight 0, so the
-// sums run branch-free and unrolled (their loads issue together).  Both LDS
-// tables a wave sweeps are laid out with the lane index fastest (dq
-// transposed to [dy][dx], the inner sums as [dx][ky]): no bank conflicts.
+// sums run branch-free and unrolled (their loads issue together).  dq is laid out
+// in LDS with the lane index fastest ([dy][dx]).
 // ---------------------------------------------------------------------------
+template <int LOGN>
+struct HqCfg {
+  static constexpr int N = 1 << LOGN, P = N / 2 + 1;     // pairs (k, n - k), k = 0 .. n/2
+  static constexpr int KP = P < 11 ? P : 11, R = 3, NG = (KP + R - 1) / R;
+  static constexpr int CH = (P + KP - 1) / KP;           // blocks per plane
+  static constexpr int KYS = 4 * ((2 * NG * R + 3) / 4); // row stride of the inner sums
+};
+
 template <int LOGN, bool ET>
 __global__ void __launch_bounds__(256)
 k_build_hq(float2* __restrict__ hq, int m, const int* __restrict__ dq,
            const double2* __restrict__ etab, const double* __restrict__ cosn, double invZ) {
-  constexpr int N = 1 << LOGN, N1 = N + 1, KYC = N1 < 32 ? N1 : 32;
+  using HC = HqCfg<LOGN>;
+  constexpr int N = HC::N, P = HC::P, KP = HC::KP, R = HC::R, NG = HC::NG, KYS = HC::KYS;
   constexpr bool DQ = N <= 64;
-  __shared__ double2 G[N * KYC];                   // [dx][ky - ky0]
+  __shared__ double2 G[N * KYS];                   // [dx][pair, then the partners]
   __shared__ double cs[2 * N];
   __shared__ int dq_l[DQ ? N * N : 1];
   extern __shared__ double2 et_l[];
-  const int kt = blockIdx.x, ky0 = blockIdx.y * KYC, tid = threadIdx.x;
-  const int nky = (N1 - ky0) < KYC ? (N1 - ky0) : KYC;
+  const int kt = blockIdx.x, kp0 = blockIdx.y * KP, tid = threadIdx.x;
   const int pmask = 2 * m - 1;
   for (int i = tid; i < 2 * N; i += blockDim.x) cs[i] = cosn[i];
   if constexpr (DQ) {
@@ -1908,35 +1921,68 @@ k_build_hq(float2* __restrict__ hq, int m, const int* __restrict__ dq,
   }
   const double2* ets = ET ? et_l : etab;
   __syncthreads();
-  // inner sum over dy for this block's ky range
-  for (int it = tid; it < nky * N; it += blockDim.x) {
-    const int kyl = it / N, dx = it % N, ky = ky0 + kyl;
-    double sr = 0.0, si = 0.0;
-#pragma unroll 8
-    for (int dy = 0; dy < N; ++dy) {
-      const int q = DQ ? dq_l[dy * N + dx] : dq[dx * N + dy];
-      const bool in = q >= 0;
-      const double2 e = ets[(kt * (in ? q : 0)) & pmask];
-      const double w = in ? (dy ? 2.0 : 1.0) * cs[(ky * dy) & (2 * N - 1)] : 0.0;
-      sr += w * e.x;
-      si += w * e.y;
+  // inner sum over dy for this block's pairs (those beyond n/2 are not stored)
+  for (int it = tid; it < NG * N; it += blockDim.x) {
+    const int grp = it / N, dx = it % N, k0 = kp0 + grp * R;
+    double2 s[R][2] = {};
+    int at[R] = {};
+#pragma unroll 2
+    for (int dy = 0; dy < N; dy += 2) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int q = DQ ? dq_l[(dy + h) * N + dx] : dq[dx * N + dy + h];
+        const bool in = q >= 0;
+        const double2 e = ets[(kt * (in ? q : 0)) & pmask];
+        const double w = in ? (dy + h ? 2.0 : 1.0) : 0.0, er = w * e.x, ei = w * e.y;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          const double c = cs[at[r]];
+          s[r][h].x = fma(c, er, s[r][h].x);
+          s[r][h].y = fma(c, ei, s[r][h].y);
+          at[r] = (at[r] + k0 + r) & (2 * N - 1);
+        }
+      }
     }
-    G[dx * KYC + kyl] = make_double2(sr, si);
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int c = dx * KYS + grp * R + r;
+      G[c] = make_double2(s[r][0].x + s[r][1].x, s[r][0].y + s[r][1].y);
+      G[c + NG * R] = make_double2(s[r][0].x - s[r][1].x, s[r][0].y - s[r][1].y);
+    }
   }
   __syncthreads();
-  // outer sum over dx
-  for (int it = tid; it < N1 * nky; it += blockDim.x) {
-    const int kyl = it / N1, kx = it % N1, ky = ky0 + kyl;
-    double ar = 0.0, ai = 0.0;
-#pragma unroll 8
-    for (int dx = 0; dx < N; ++dx) {
-      const double w = (dx ? 2.0 : 1.0) * cs[(kx * dx) & (2 * N - 1)];
-      const double2 gv = G[dx * KYC + kyl];
-      ar += w * gv.x;
-      ai += w * gv.y;
+  // outer sum over dx: columns c of G, four at a time
+  for (int it = tid; it < P * (KYS / 4); it += blockDim.x) {
+    const int grp = it / P, kp = it % P;
+    double2 a[4][2] = {};
+    int at = 0;
+#pragma unroll 2
+    for (int dx = 0; dx < N; dx += 2) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const double c = (dx + h ? 2.0 : 1.0) * cs[at];
+        at = (at + kp) & (2 * N - 1);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const double2 g = G[(dx + h) * KYS + 4 * grp + r];
+          a[r][h].x = fma(c, g.x, a[r][h].x);
+          a[r][h].y = fma(c, g.y, a[r][h].y);
+        }
+      }
     }
-    const float2 v = make_float2((float)(ar * invZ), (float)(ai * invZ));
-    hq_store<LOGN>(hq + (size_t)kt * hq_pitch(LOGN), kx, ky, v);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int c = 4 * grp + r, kq = c < NG * R ? c : c - NG * R, kl = kp0 + kq;
+      if (c >= 2 * NG * R || kq >= KP || kl > N / 2) continue;
+      const int ky = c < NG * R ? kl : N - kl;
+      if (c >= NG * R && ky == kl) continue;               // n/2 is its own partner
+      float2* Hk = hq + (size_t)kt * hq_pitch(LOGN);
+      hq_store<LOGN>(Hk, kp, ky, make_float2((float)((a[r][0].x + a[r][1].x) * invZ),
+                                             (float)((a[r][0].y + a[r][1].y) * invZ)));
+      if (kp < N / 2)
+        hq_store<LOGN>(Hk, N - kp, ky, make_float2((float)((a[r][0].x - a[r][1].x) * invZ),
+                                                   (float)((a[r][0].y - a[r][1].y) * invZ)));
+    }
   }
 }
 
@@ -2174,18 +2220,16 @@ __global__ void __launch_bounds__(256) k_hq_pack_real(float2* __restrict__ hq, i
 
 hipError_t launch_build_hq(int logn, int logm, float2* hq, const int* dq, const double2* etab,
                            const double* cosn, double invZ, hipStream_t st) {
-  const int m = 1 << logm, n1 = (1 << logn) + 1;
-  const int kyc = n1 < 32 ? n1 : 32;
-  const dim3 grid(m + 1, (n1 + kyc - 1) / kyc);
+  const int m = 1 << logm;
   const bool et = 2 * m <= kHqStagedExp;
 #define CNLOS_HQ(LN)                                                                           \
   case LN:                                                                                     \
     if (et)                                                                                    \
-      hipLaunchKernelGGL((k_build_hq<LN, true>), grid, dim3(256), 2 * m * sizeof(double2), st,  \
-                         hq, m, dq, etab, cosn, invZ);                                         \
+      hipLaunchKernelGGL((k_build_hq<LN, true>), dim3(m + 1, HqCfg<LN>::CH), dim3(256),         \
+                         2 * m * sizeof(double2), st, hq, m, dq, etab, cosn, invZ);            \
     else                                                                                       \
-      hipLaunchKernelGGL((k_build_hq<LN, false>), grid, dim3(256), 0, st, hq, m, dq, etab,      \
-                         cosn, invZ);                                                          \
+      hipLaunchKernelGGL((k_build_hq<LN, false>), dim3(m + 1, HqCfg<LN>::CH), dim3(256), 0, st, \
+                         hq, m, dq, etab, cosn, invZ);                                         \
     break;
   switch (logn) {
     CNLOS_HQ(3)
