@@ -543,7 +543,6 @@ hipError_t conv(cnlos_problem* p, const ConvSrc& src, bool adjoint, int epi, con
 cnlos_status power_estimate(cnlos_problem* p, const Batch& bt, cnlos_problem* const* mem,
                             bool masked, double* est) {
   float* X = p->AU[0];
-  float* Y = p->AU[1];
   for (int i = 0; i < bt.nz; ++i)
     HIPCHK(launch_fill(zsh_host(X, i * bt.zs), p->V, (float)(1.0 / sqrt((double)p->V)), p->st));
   for (int it = 0; it < p->cfg.power_iters; ++it) {
@@ -552,25 +551,20 @@ cnlos_status power_estimate(cnlos_problem* p, const Batch& bt, cnlos_problem* co
     s1.b = fixed(nullptr);
     s1.scale_div = it > 0 ? &p->ctl->pow_est : nullptr;
     ConvEpi e1{};
-    e1.out = fixed(Y);
+    e1.out = fixed(nullptr);
     e1.au = fixed(nullptr);
     e1.au_prev = fixed(nullptr);
     e1.w = p->wk;
     e1.mask = masked ? p->mask : nullptr;
-    HIPCHK(launch_conv(p->logn, p->logm, p->tb, s1, p->spec, false, EPI_PLAIN, e1, nullptr, bt,
+    HIPCHK(launch_conv(p->logn, p->logm, p->tb, s1, p->spec, false, EPI_NORMAL, e1, nullptr, bt,
                        p->st, &p->prof));
-    ConvSrc s2{};
-    s2.a = fixed(Y);
-    s2.b = fixed(nullptr);
-    s2.w = p->wk;
-    s2.mask = masked ? p->mask : nullptr;
     ConvEpi e2{};
     e2.out = fixed(X);
     e2.au = fixed(nullptr);
     e2.au_prev = fixed(nullptr);
     e2.partials = p->partials;
-    HIPCHK(launch_conv(p->logn, p->logm, p->tb, s2, p->spec, true, EPI_NORM, e2, nullptr, bt,
-                       p->st, &p->prof));
+    HIPCHK(launch_conv(p->logn, p->logm, p->tb, ConvSrc{}, p->spec, true, EPI_NORM, e2, nullptr, bt,
+                       p->st, &p->prof, true));
     HIPCHK(launch_pow_finalize(p->ctl, p->partials, p->nb_conv, bt, p->st));
   }
   for (int i = 0; i < bt.nz; ++i) {

@@ -229,7 +229,9 @@ struct ConvSrc {
   int lincache;
 };
 
-enum Epi : int { EPI_PLAIN = 0, EPI_FWD_OBJ = 1, EPI_FWD_DUAL = 2, EPI_NORM = 3 };
+// EPI_NORMAL: the output, weighted and masked once more, goes through the
+// forward t pass of the adjoint that follows (launch_conv with tfwd_done)
+enum Epi : int { EPI_PLAIN = 0, EPI_FWD_OBJ = 1, EPI_FWD_DUAL = 2, EPI_NORM = 3, EPI_NORMAL = 4 };
 
 // Epilogue of the t-axis inverse pass of a convolution.
 struct ConvEpi {

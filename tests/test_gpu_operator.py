@@ -151,3 +151,27 @@ def test_plane_kernels_on_short_time_axes(n, m):
     assert rel_l2(to_host(P.apply_A(to_dev(torch, u))), O.apply_A(u, op)) <= TOL_OP
     assert rel_l2(to_host(P.apply_AT(to_dev(torch, y), True)), O.apply_AT(y, op, True)) <= TOL_OP
     P.close()
+
+
+# every transform length of the column passes (lane groups of one wave, register
+# passes of 4, 8 and 16 elements, the long form): both directions on full
+# volumes, and the step estimate, whose iteration runs A and A^T through their
+# fused t pass (the tolerance is the one of the estimate's other tests)
+@pytest.mark.parametrize("m", [16, 32, 64, 128, 256, 512, 1024, 2048])
+def test_column_passes_of_every_length(m):
+    torch = need_gpu()
+    n, bin_ps = 8, 16.0 * 512 / m
+    say(f"column passes m={m}")
+    mask = _mask(n, 11 + m)
+    cfg = C.default_config(nx=n, ny=n, nt=m, wall_w_m=0.9, wall_h_m=0.9, bin_ps=bin_ps,
+                           model=C.MODEL_OBJECT, max_iters=4, L0=0.0)
+    P = C.Problem(cfg, mask)
+    op = O.make_operator(n, n, m, 0.9, 0.9, bin_ps, O.FALLOFF_COMPENSATED, mask)
+    u = f32(scenes.random_volume((n, n, m), seed=n * 79 + m))
+    y = f32(scenes.random_signed((n, n, m), seed=n * 79 + m + 1))
+    assert rel_l2(to_host(P.apply_A(to_dev(torch, u))), O.apply_A(u, op)) <= TOL_OP
+    assert rel_l2(to_host(P.apply_AT(to_dev(torch, y), True)), O.apply_AT(y, op, True)) <= TOL_OP
+    L0 = 2.0 * O.power_norm2(lambda v: O.apply_A(v, op, True), lambda v: O.apply_AT(v, op, True),
+                             (n, n, m), cfg.power_iters)
+    assert abs(P.info()["L0_obj"] - L0) <= 1e-5 * L0
+    P.close()
