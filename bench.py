@@ -584,7 +584,7 @@ def algorithmic_flops(kind, n, m):
 def kernel_source_hash():
     h = hashlib.sha256()
     for name in ("k_spectral.hip", "k_admm.hip", "fft_device.h", "cnlos_internal.h",
-                 "stencil_device.h"):
+                 "stencil_device.h", "fft_quad.h", "fft_column.h"):
         with open(os.path.join(ROOT, "paper_2301_00406_amd", "csrc", name), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]

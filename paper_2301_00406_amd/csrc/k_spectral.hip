@@ -42,13 +42,12 @@ __device__ __forceinline__ float* vol_out(const Vol& v, const CtlHead& h, size_t
 // bound by the latency of their phases, and fewer waves hide less of it.
 // ---------------------------------------------------------------------------
 // Columns per block of a t pass of length 2^logf: 8 for lengths 256 to 1024,
-// where a block's 512 threads, about 60 KB of LDS (at 512) and its registers
+// where a block's 512 threads, its LDS (37 KB at 512, 75 KB at 1024) and registers
 // leave room for two blocks per CU, so one block's loads overlap the other's
-// transform (measured faster than 16-column blocks of 1024 threads with
-// 128-byte segments, one per CU: 61.7 against 62.6 ms per 64x64x512
-// reconstruction, 408 against 442 ms for a batch of eight); 16 for shorter
-// transforms (the solve phase of a fused pass needs whole waves), 4 at 2048
-// (LDS).
+// transform (16-column blocks of 1024 threads, one per CU, write 128-byte
+// segments: forward pass of 128x128x1024 84 -> 73 us, but inverse 60 -> 77, and
+// 13 -> 18 and 11 -> 17 at 32x32x1024); 16 for shorter transforms (the solve phase
+// of a fused pass needs whole waves), 4 at 2048 (LDS).
 constexpr int t_columns(int logf) { return logf <= 7 ? 16 : (logf <= 10 ? 8 : 4); }
 
 // waves per SIMD that a t pass is compiled for: two blocks of 512 threads per CU
@@ -1134,9 +1133,9 @@ k_plane_conv_quad(float2* __restrict__ spec, const float2* __restrict__ hq,
 // n = 128: the padded plane does not fit LDS, so the ky halves follow one
 // another through Y [n][n], and a lane group takes one column; waves 4 to 7
 // take the partner columns of waves 0 to 3 and read the same kernel values.
-// 128x128x1024: 313 us on eight-lane transforms -> 243, of which about 140 are
-// vector issue; the rest is memory (the plane is read twice and its first half
-// written and read back) between barriers that all eight waves meet.
+// 128x128x1024: 313 us on eight-lane transforms -> 237, of which about 140 are
+// vector issue; the rest is the latency that two waves per SIMD leave open between
+// barriers that all eight meet (planes and H^ held in L2: 222, so not memory).
 template <int LOGN, bool ADJ, int PAD, bool PACKED>
 __device__ __forceinline__ void plane_conv_wide_body(float2* __restrict__ P, const float2* Hp,
                                                      float2* Y, float2* tw2, float2 tv, int tid) {
