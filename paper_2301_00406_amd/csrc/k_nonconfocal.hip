@@ -410,7 +410,7 @@ k_nc_transpose(NcGeo g, const float* __restrict__ tau, float* __restrict__ u) {
 
 }  // namespace
 
-// Histograms and columns of the forward kernel: at most 58 KiB with the counts
+// Histograms and columns of the forward kernel: at most 60 KiB with the counts
 // of waves and detectors that launch_nc_forward takes.
 static size_t nc_forward_lds_bytes(int m, int d, int waves) {
   const size_t s = (m + 63) / 64;
