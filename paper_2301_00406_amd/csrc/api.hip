@@ -293,6 +293,72 @@ void Prof::release() {
   pool.clear();
 }
 
+// The resampling rows and columns as the t passes read them, from the R_z table
+// of eq. (3); the reason when they do not fit what the t passes assume.
+const char* resample_descriptors(int m, std::vector<float4>& srows, std::vector<float4>& scols) {
+  // R_z as overlap lengths of [sqrt(q/m), sqrt((q+1)/m)) with [k/m, (k+1)/m), times m
+  std::vector<std::vector<std::pair<int, double>>> rows(m), cols(m);
+  for (int q = 0; q < m; ++q) {
+    const double lo = sqrt((double)q / m), hi = sqrt((double)(q + 1) / m);
+    int k0 = (int)floor(lo * m) - 1;
+    if (k0 < 0) k0 = 0;
+    int k1 = (int)ceil(hi * m) + 1;
+    if (k1 > m - 1) k1 = m - 1;
+    for (int k = k0; k <= k1; ++k) {
+      const double a = fmax(lo, (double)k / m), b = fmin(hi, (double)(k + 1) / m);
+      if (b > a) {
+        rows[q].push_back({k, m * (b - a)});
+        cols[k].push_back({q, m * (b - a)});
+      }
+    }
+  }
+  // One descriptor per row and column.  At most 3 taps: the weights of three
+  // neighbouring samples from a base on (clamped so that all three exist).
+  // Longer R_z rows: the t pass computes them from prefix sums of the first
+  // resample_scan_rows lane-rows of the column, takes their interior weights as
+  // 1, and expects them below resample_long_rows: check all three.
+  auto bits = [](int x) {
+    float f;
+    memcpy(&f, &x, sizeof(f));
+    return f;
+  };
+  auto describe = [&](const std::vector<std::pair<int, double>>& v) {
+    const int base = v.empty() ? 0 : std::min(v[0].first, m - 3);
+    float w[3] = {0.f, 0.f, 0.f};
+    for (const auto& t : v) w[t.first - base] = (float)t.second;
+    return make_float4(w[0], w[1], w[2], bits(base | (base + 2) << 12));
+  };
+  srows.assign(m, float4{});
+  scols.assign(m, float4{});
+  const int lanes = m / 2 < 64 ? m / 2 : 64;
+  const int scan_end = resample_scan_rows(m, lanes) * lanes;
+  for (int q = 0; q < m; ++q) {
+    const auto& v = rows[q];
+    for (size_t t = 0; t < v.size(); ++t)
+      if (v[t].first != v[0].first + (int)t) return "resampling row not contiguous";
+    if (v.size() <= 3) {
+      srows[q] = describe(v);
+      continue;
+    }
+    const int k0 = v[0].first, k2 = v.back().first;
+    if (k2 + 1 > scan_end || q >= resample_long_rows(m))
+      return "long resampling row beyond the prefix-summed range";
+    for (size_t t = 1; t + 1 < v.size(); ++t)
+      if ((float)v[t].second != 1.f) return "resampling interior weight is not 1";
+    srows[q] = make_float4((float)v[0].second, 0.f, (float)v.back().second,
+                           bits(k0 | k2 << 12 | 1 << 24));
+  }
+  for (int k = 0; k < m; ++k) {
+    const auto& v = cols[k];
+    if (v.size() > 3) return "resampling column of more than 3 taps";
+    for (size_t t = 0; t < v.size(); ++t)
+      if (v[t].first != v[0].first + (int)t) return "resampling column not contiguous";
+    scols[k] = describe(v);
+    scols[k].w = bits(v.empty() ? 0 : std::min(v[0].first, m - 3));
+  }
+  return nullptr;
+}
+
 }  // namespace cnlos
 
 namespace {
@@ -1134,65 +1200,8 @@ cnlos_status build_tables(cnlos_problem* p, const cnlos_config* cfg, const uint8
     return t;
   };
   const std::vector<float2> twc_t = per_span(m), twc_xy = per_span(2 * n);
-  // R_z as overlap lengths of [sqrt(q/m), sqrt((q+1)/m)) with [k/m, (k+1)/m), times m
-  std::vector<std::vector<std::pair<int, double>>> rows(m), cols(m);
-  for (int q = 0; q < m; ++q) {
-    const double lo = sqrt((double)q / m), hi = sqrt((double)(q + 1) / m);
-    int k0 = (int)floor(lo * m) - 1;
-    if (k0 < 0) k0 = 0;
-    int k1 = (int)ceil(hi * m) + 1;
-    if (k1 > m - 1) k1 = m - 1;
-    for (int k = k0; k <= k1; ++k) {
-      const double a = fmax(lo, (double)k / m), b = fmin(hi, (double)(k + 1) / m);
-      if (b > a) {
-        rows[q].push_back({k, m * (b - a)});
-        cols[k].push_back({q, m * (b - a)});
-      }
-    }
-  }
-  // One descriptor per row and column.  At most 3 taps: the weights of three
-  // neighbouring samples from a base on (clamped so that all three exist).
-  // Longer R_z rows: the t pass computes them from prefix sums of the first
-  // resample_scan_rows lane-rows of the column, takes their interior weights as
-  // 1, and expects them below resample_long_rows: check all three.
-  auto bits = [](int x) {
-    float f;
-    memcpy(&f, &x, sizeof(f));
-    return f;
-  };
-  auto describe = [&](const std::vector<std::pair<int, double>>& v) {
-    const int base = v.empty() ? 0 : std::min(v[0].first, m - 3);
-    float w[3] = {0.f, 0.f, 0.f};
-    for (const auto& t : v) w[t.first - base] = (float)t.second;
-    return make_float4(w[0], w[1], w[2], bits(base | (base + 2) << 12));
-  };
-  std::vector<float4> srows(m), scols(m);
-  const int lanes = m / 2 < 64 ? m / 2 : 64;
-  const int scan_end = resample_scan_rows(m, lanes) * lanes;
-  for (int q = 0; q < m; ++q) {
-    const auto& v = rows[q];
-    for (size_t t = 0; t < v.size(); ++t)
-      if (v[t].first != v[0].first + (int)t) return fail(CNLOS_EINVAL, "resampling row not contiguous");
-    if (v.size() <= 3) {
-      srows[q] = describe(v);
-      continue;
-    }
-    const int k0 = v[0].first, k2 = v.back().first;
-    if (k2 + 1 > scan_end || q >= resample_long_rows(m))
-      return fail(CNLOS_EINVAL, "long resampling row beyond the prefix-summed range");
-    for (size_t t = 1; t + 1 < v.size(); ++t)
-      if ((float)v[t].second != 1.f) return fail(CNLOS_EINVAL, "resampling interior weight is not 1");
-    srows[q] = make_float4((float)v[0].second, 0.f, (float)v.back().second,
-                           bits(k0 | k2 << 12 | 1 << 24));
-  }
-  for (int k = 0; k < m; ++k) {
-    const auto& v = cols[k];
-    if (v.size() > 3) return fail(CNLOS_EINVAL, "resampling column of more than 3 taps");
-    for (size_t t = 0; t < v.size(); ++t)
-      if (v[t].first != v[0].first + (int)t) return fail(CNLOS_EINVAL, "resampling column not contiguous");
-    scols[k] = describe(v);
-    scols[k].w = bits(v.empty() ? 0 : std::min(v[0].first, m - 3));
-  }
+  std::vector<float4> srows, scols;
+  if (const char* why = resample_descriptors(m, srows, scols)) return fail(CNLOS_EINVAL, why);
   std::vector<float2> fa, fb;
   column_twiddles(p->logm, fa, fb);
   if ((int)std::max(fa.size(), fb.size()) * 2 > column_tw_floats(m))

@@ -311,6 +311,21 @@ constexpr int resample_scan_rows(int M, int G) {
 
 // R_z rows of more than 3 taps lie below this bin (the table builder checks it).
 constexpr int resample_long_rows(int M) { return M / 8; }
+// The descriptors' lanes w: k0 | k2 << 12 | long << 24 (rz_row).  What the rows
+// read of a column: samples k0, k0 + 1 and k2, and for a row of more than 3 taps
+// the prefix sums p0 and p2.  Only the first resample_scan_rows lane-rows of the
+// prefix sums exist, and a row of at most 3 taps may lie anywhere: it reads the
+// first one twice.
+struct RzIndex {
+  int k0, k2, p0, p2;
+  bool lg;
+};
+__host__ __device__ constexpr RzIndex rz_index(int bits) {
+  const int k0 = bits & 0xfff, k2 = (bits >> 12) & 0xfff;
+  const bool lg = (bits >> 24) != 0;
+  return {k0, k2, lg ? k0 + 1 : 0, lg ? k2 : 0, lg};
+}
+const char* resample_descriptors(int m, std::vector<float4>& rows, std::vector<float4>& cols);
 void column_twiddles(int logm, std::vector<float2>& fa, std::vector<float2>& fb);
 
 // XCD-aware block order.  Workgroups are dealt round-robin over the 8 XCDs,

@@ -285,15 +285,13 @@ __device__ __forceinline__ void zsh_tw(TwTabs& t, size_t zo) {
 // sums pf.  Such rows lie below m/8 (resample_long_rows; LONG: the row may be one).
 template <bool LONG, typename PT>
 __device__ __forceinline__ float rz_row(const float4 d, const float* xf, const PT* pf) {
-  const int bits = __float_as_int(d.w), k0 = bits & 0xfff;
-  const float s = fmaf(d.y, xf[k0 + 1], d.x * xf[k0]);
+  const RzIndex x = rz_index(__float_as_int(d.w));
+  const float s = fmaf(d.y, xf[x.k0 + 1], d.x * xf[x.k0]);
   if constexpr (!LONG) {
-    return fmaf(d.z, xf[k0 + 2], s);
+    return fmaf(d.z, xf[x.k0 + 2], s);
   } else {
-    const bool lg = (bits >> 24) != 0;
-    const int k2 = (bits >> 12) & 0xfff;                 // k0 + 2, or the row's end
-    const float in = (float)(pf[k2] - pf[k0 + 1]);
-    return fmaf(d.z, xf[k2], s + (lg ? in : 0.f));
+    const float in = (float)(pf[x.p2] - pf[x.p0]);
+    return fmaf(d.z, xf[x.k2], s + (x.lg ? in : 0.f));   // k2: k0 + 2, or the row's end
   }
 }
 __device__ __forceinline__ float st_taps(const float4 d, const float* g) {
