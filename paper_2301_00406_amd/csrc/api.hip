@@ -919,10 +919,13 @@ cnlos_status group_start(Group& g, std::vector<SceneRun>& runs, int32_t iters) {
 
 // Enqueue up to `batch` iteration slots for the group's active members (the
 // sequences each slot needs follow from the members' last known state).
-// Sets *enqueued to whether anything was enqueued.
-cnlos_status group_enqueue(Group& g, const std::vector<SceneRun>& runs, int batch, bool* enqueued) {
+// catch_up: while some members are still in their warm start, only as many as
+// the last of them needs to end it.  Sets *enqueued to whether anything was
+// enqueued.
+cnlos_status group_enqueue(Group& g, const std::vector<SceneRun>& runs, int batch, bool catch_up,
+                           bool* enqueued) {
   cnlos_problem* p = g.lead;
-  int need = 0, to_s1end = 0x7fffffff;
+  int need = 0, to_s1end = 0x7fffffff, last_s1end = 0;
   bool s1 = false, s2 = false;
   for (size_t i = 0; i < g.mem.size(); ++i) {
     if (!runs[i].active) continue;
@@ -931,6 +934,7 @@ cnlos_status group_enqueue(Group& g, const std::vector<SceneRun>& runs, int batc
     if (h.stage == 1 && h.iter < h.stage1_end) {
       s1 = true;
       to_s1end = std::min(to_s1end, h.stage1_end - h.iter);
+      last_s1end = std::max(last_s1end, h.stage1_end - h.iter);
     } else {
       s2 = true;
     }
@@ -940,6 +944,9 @@ cnlos_status group_enqueue(Group& g, const std::vector<SceneRun>& runs, int batc
   int nb = std::min(batch, need);
   // a warm-start batch ends where the first scene reaches the hand-over
   if (s1 && !s2) nb = std::min(nb, to_s1end);
+  // from then on a slot holds both sequences and the hand-over, until the host
+  // knows that no scene needs the first two
+  if (s1 && s2 && catch_up) nb = std::min(nb, last_s1end);
   for (int j = 0; j < nb; ++j) {
     int seq = 0;
     for (size_t i = 0; i < g.mem.size(); ++i) {
@@ -1033,7 +1040,7 @@ cnlos_status run_groups(std::vector<Group>& gs, int32_t iters, std::vector<cnlos
     std::vector<char> busy(gs.size(), 0);
     for (size_t gi = 0; gi < gs.size(); ++gi) {
       bool e = false;
-      cnlos_status s = group_enqueue(gs[gi], runs[gi], batch, &e);
+      cnlos_status s = group_enqueue(gs[gi], runs[gi], batch, true, &e);
       if (s != CNLOS_OK) return s;
       busy[gi] = e;
       any = any || e;
@@ -2348,7 +2355,7 @@ cnlos_status cnlos_server_step(cnlos_server* sv, int32_t* active, int32_t* queue
       }
     if (v.mem.empty()) continue;
     bool e = false;
-    cnlos_status st = group_enqueue(v, g->vruns, sv->rounds, &e);
+    cnlos_status st = group_enqueue(v, g->vruns, sv->rounds, false, &e);
     if (st != CNLOS_OK) return st;
     if (hipEventRecord(g->done, g->st) != hipSuccess) return fail(CNLOS_EHIP, "hipEventRecord failed");
     g->busy = true;

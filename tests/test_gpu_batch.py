@@ -140,3 +140,31 @@ def test_batch_member_failure_does_not_stop_the_others():
     alone = _alone(torch, *items[1], cfgs[1])
     assert np.array_equal(B.members[1].volume().cpu().numpy(), alone[0])
     B.close()
+
+
+def test_member_behind_in_its_warm_start_costs_only_its_own_slots():
+    """One member's rejections leave it in the warm start when the other is done:
+    slots that hold both stages and the hand-over are enqueued for what it still
+    needs, not for the rest of the run."""
+    torch = need_gpu()
+    say("batch: a dual member behind by its rejections, launches counted")
+    items = [_scene(16, 128, 1000 + i) for i in range(2)]
+    cfgs = [_cfg(sc, C.MODEL_DUAL, DUAL, init_iters=4, max_iters=60, L0=l0)
+            for (sc, _), l0 in zip(items, (1e-3, 0.0))]
+    B = C.Batch(cfgs, [sc.mask for sc, _ in items])
+    for m, (_, raw) in zip(B.members, items):
+        m.set_measurement(to_dev(torch, raw))
+    B.members[0].profile_enable(["post", "other"])
+    st, reps = B.run()
+    launches = {k: v[1] for k, v in B.members[0].profile_read().items()}
+    assert st == C.OK, C.last_error()
+    assert [r["iters_done"] for r in reps] == [64, 64]
+    rejects = max(r["bt_rejects"] for r in reps)
+    say(f"rejections {[r['bt_rejects'] for r in reps]}, launches {launches}")
+    assert reps[0]["bt_rejects"] > 0
+    # each rejection puts a member one slot back; 4 slots to the first hand-over
+    assert launches["other"] <= 4 + rejects
+    # one post launch per stage and slot
+    assert launches["post"] <= 64 + rejects + 2 * (4 + rejects)
+    _check_members(torch, B, items, cfgs)
+    B.close()
