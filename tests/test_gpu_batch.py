@@ -168,3 +168,21 @@ def test_member_behind_in_its_warm_start_costs_only_its_own_slots():
     assert launches["post"] <= 64 + rejects + 2 * (4 + rejects)
     _check_members(torch, B, items, cfgs)
     B.close()
+
+
+def test_run_that_fails_at_once_leaves_few_slots_behind():
+    """Without a stopping rule many slots are enqueued per wait, but not before the
+    first ones are known to have gone well."""
+    torch = need_gpu()
+    say("a run of 64 iterations that fails in its first slot, launches counted")
+    sc, raw = _scene(16, 128, 1100)
+    P = C.Problem(_cfg(sc, C.MODEL_OBJECT, OBJ, max_iters=64, L0=1e-9, bt_max_trials=0), sc.mask)
+    P.set_measurement(to_dev(torch, raw))
+    P.profile_enable(["post"])
+    with pytest.raises(C.CnlosError) as e:
+        P.run()
+    assert e.value.status == C.EBACKTRACK
+    launches = P.profile_read()["post"][1]
+    say(f"{launches} slots")
+    assert launches <= 4
+    P.close()
