@@ -522,8 +522,8 @@ def serve_workload(torch, C, scenes, n_req, rate, seed=5000, baseline=True):
 def hq_bytes(n, m, layout=False):
     """Bytes of the kernel spectrum H^ per convolution: the quarter (n + 1)^2
     of each kt plane that its evenness in kx and ky determines (the method's
-    own bytes), or the 2n x 2n entries per plane that the workspace holds room
-    for (the layout's bytes)."""
+    own bytes), or with `layout` the 2n x 2n entries per plane that a workspace
+    holds room for (hq_table_bytes: what a convolution reads)."""
     return (m + 1) * (4 * n * n if layout else (n + 1) * (n + 1)) * 8
 
 

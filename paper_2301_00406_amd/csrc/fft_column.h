@@ -6,7 +6,8 @@
 // one of 1024: radix 4), natural order in, with lane twiddles from tables laid
 // out in lane order; between passes registers and lane bits change places, by
 // v_permlane swaps and row DPP or through the column's own LDS, which only its
-// wave touches (no barrier).  Other lengths: radix-2 stages, in registers for
+// wave touches (no barrier).  Other lengths (2 values per lane at 128 and below,
+// 32 at 2048; passes were not tried there): radix-2 stages, in registers for
 // spans of G and more and across lanes below (fft_device.h).  At 512 points the
 // passes take 0.6 of the vector instructions and 16 instead of 64 LDS exchanges.
 #pragma once

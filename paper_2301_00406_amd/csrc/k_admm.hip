@@ -19,11 +19,11 @@ constexpr int kCtlThreads = 1024;
 // Blocks of the stencil kernels: two bin pairs per thread, up to a cap that the
 // volume sets.  A block of the post kernels costs its share of the backtracking
 // decision (the check and step partials) and an FP64 block sum whatever it
-// works on, so one pair per thread, and blocks without any, lose more than the
-// waves they add: per iteration of the dual model (with every block busy and
-// two pairs per thread, against up to one voxel per thread, half of the blocks
-// idle) eight scenes of 32x32x256 together 235 -> 193 us, one 88.6 -> 79.9
-// (these figures include the plane kernels' change from eight to four lanes).
+// works on, so a block without work costs nearly as much as one with it: with a
+// thread per voxel, half of the blocks idle, an iteration of the dual model takes
+// 220 instead of 181 us for eight scenes of 32x32x256 together, 109 instead of 97
+// for one of 32x32x512, 81 instead of 76 for one of 32x32x256.  One pair per thread
+// measures as two do (182.5, 98 and 75 us); two leave half of the partials.
 // Each block walks a contiguous range of bin pairs, and all blocks of an XCD
 // read the neighbour rows of each other's ranges at about the same time, so how
 // many run at once decides whether those reads still find the data in L2.

@@ -26,7 +26,7 @@
 // since d_d = d_d^2 r and 1 / d_d^2 = r^2, and a product with 1 / (c dt) instead
 // of the bin's division.  That product can fall on the other side of a whole
 // number only when it is within a few rounding errors of one: such paths
-// (kNearBin; about one in 10^7) take the plain form, so every bin is the one
+// (kNearBin; one in 5 10^7) take the plain form, so every bin is the one
 // that the plain form gives.
 #include "cnlos_internal.h"
 
@@ -83,9 +83,9 @@ __device__ __forceinline__ double nc_rsqrt(double x) {
 
 // z for the body of a rarely taken branch.  The compiler counts a square root
 // or a division as one operation: it would compute the body for every path,
-// or lift a root out of two such bodies (30.9 and 14.8 ms at 64x64x512 with
-// one and two detectors per block); a value that it cannot see through keeps
-// them where they are.
+// or lift a root out of two such bodies (64x64x512, when the branch was made: 30.9
+// and 14.8 ms with one and two detectors per block, 13.8 and 12.4 without); a
+// value that it cannot see through keeps them where they are.
 __device__ __forceinline__ double nc_in_branch(double z) {
   asm volatile("" : "+v"(z));
   return z;
@@ -155,7 +155,7 @@ __device__ __forceinline__ int nc_steps(const NcGeo& g, double lat_i, double lat
 // A column's u is read coalesced (SM >= S loads, the next column's while this
 // one is summed) and handed to the lanes through LDS: read in place, at a
 // stride of S floats, the columns of a CU's waves overrun its L1 (64x64x512,
-// one detector per block: 15.0 against 13.8 ms).
+// one detector per block, when it was made: 15.0 against 13.8 ms).
 // Consecutive depths in consecutive lanes, with a segmented scan over equal
 // bins per 64 paths (18 lane exchanges through the LDS pipe), and the plain path
 // arithmetic took 42.6 ms at 64x64x512 and 1.59 ms at 32x32x256; now 10.5
@@ -430,11 +430,15 @@ hipError_t launch_nc_forward(const NcGeo& g0, const float* u, float* tau, hipStr
   g.plain = nc_in_range(g) ? 0 : 1;
   // Two detectors per block share a voxel's illumination path, but their
   // histograms leave room for half the waves.  Measured, one against two
-  // detectors: 24x24x224 237 / 263 us, 32x32x256 515 / 462, 45x45x300
-  // 2284 / 1985, 64x64x512 13.8 / 12.4 ms, 40x40x1000 5.9 / 8.7 ms.  Eight waves
-  // while two blocks of them find room on a CU, with registers for both, else
-  // four: eight against four, 24x24x512 400 / 424 us, 24x24x560 583 / 476,
-  // 33x33x320 727 / 790, 64x64x512 (two detectors) 15.5 / 12.4 ms.
+  // detectors with the better count of waves each: 16x16x128 37 / 50 us, 24x24x224
+  // 216 / 218, 28x28x256 376 / 299, 32x32x256 494 / 390, 45x45x300 2240 / 1701,
+  // 64x64x512 12.5 / 10.5 ms, 32x32x576 1168 / 912 us, 40x40x600 3.00 / 2.86 ms,
+  // 40x40x1000 5.31 / 6.36 ms.  The line is the one of an earlier form of the
+  // kernel (at 24x24x224 two were 10 % slower there): from n = 24 to 31 at 256 bins
+  // and from 513 to about 600 bins it now leaves up to a fifth.  Eight waves while
+  // two blocks of them find room on a CU, with registers for both, else four:
+  // eight against four, 24x24x512 (one detector) 369 / 406 us, 33x33x320 (two)
+  // 712 / 787; 24x24x560 569 / 472, 64x64x512 (two) 13.1 / 10.5 ms.
   const bool two = g.n >= 32 && g.m <= 512;
   const int waves = nc_forward_lds_bytes(g.m, two ? 2 : 1, 8) <= 60 * 1024 ? 8 : 4;
   const int nd = g.n * g.n;

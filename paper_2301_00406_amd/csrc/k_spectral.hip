@@ -51,7 +51,8 @@ __device__ __forceinline__ float* vol_out(const Vol& v, const CtlHead& h, size_t
 constexpr int t_columns(int logf) { return logf <= 7 ? 16 : (logf <= 10 ? 8 : 4); }
 
 // waves per SIMD that a t pass is compiled for: two blocks of 512 threads per CU
-// at length 1024 (their LDS allows it; the epilogues' registers need the cap)
+// at length 1024 (their LDS allows it; the epilogues' registers need the cap, which
+// spills 12 of k_tinv_conv_rhs<FWD_DUAL>'s and 8 of k_tinv_conv<FWD_OBJ>'s)
 constexpr int t_waves(int logf) { return logf == 10 ? 4 : 1; }
 
 template <int LOGF>
@@ -63,31 +64,10 @@ struct TGeo {                                 // transform of length F = 2^LOGF
   static constexpr int NT = J * G;
 };
 
-// Block-strided copies with compile-time extents.  A loop whose trip count
-// depends on the thread index is not unrolled, and each of its iterations
-// then waits for its own load before its store; here a thread issues up to 8
-// loads (indices clamped into range) before its first store.
-template <int NT, int COUNT, typename Ld, typename St>
-__device__ __forceinline__ void block_copy(int tid, Ld ld, St st) {
-  constexpr int NS = (COUNT + NT - 1) / NT, CH = NS < 8 ? NS : 8;
-#pragma unroll
-  for (int c0 = 0; c0 < NS; c0 += CH) {
-    decltype(ld(0)) v[CH];
-#pragma unroll
-    for (int j = 0; j < CH; ++j) {
-      const int it = tid + (c0 + j) * NT;
-      v[j] = ld(it < COUNT ? it : COUNT - 1);
-    }
-#pragma unroll
-    for (int j = 0; j < CH; ++j) {
-      const int it = tid + (c0 + j) * NT;
-      if (c0 + j < NS && it < COUNT) st(it, v[j]);
-    }
-  }
-}
-
-// A block-strided copy split into its loads (into registers, indices clamped
-// into range) and its stores.  Copies whose loads are all issued before the
+// A block-strided copy with compile-time extents, split into its loads (into
+// registers, indices clamped into range) and its stores: a loop whose trip count
+// depends on the thread index is not unrolled, and each of its iterations waits
+// for its own load before its store.  Copies whose loads are all issued before the
 // first store (copy_together) cost one memory round trip together, where
 // copies done one after the other wait for each in turn.
 template <int NT, int COUNT, typename T, typename Ld, typename St>
@@ -1003,8 +983,8 @@ __device__ __forceinline__ void quad_columns(float2* const (&Yc)[NC], const floa
 }
 
 // n <= 64: a block per kt plane, Y [n][2 n] with the even ky first.  Bound by
-// vector issue (64x64x512: 80 % of the SIMDs' cycles, 0.58 of the instructions
-// of the eight-lane form, whose cross-lane stages took half of them).
+// vector issue (64x64x512: 82 % of the SIMDs' busy cycles, 47 % of each wave's; 0.58
+// of the instructions of the eight-lane form, whose cross-lane stages took half).
 // SPLIT = 1 (n = 64): 4 n threads; a lane group takes both ky halves of its row
 // and the columns ky and -ky.  SPLIT = 2 (n <= 32): 8 n threads; the second half
 // of the waves takes the odd ky and the columns -ky, and the two halves of a
@@ -1131,9 +1111,12 @@ k_plane_conv_quad(float2* __restrict__ spec, const float2* __restrict__ hq,
 // n = 128: the padded plane does not fit LDS, so the ky halves follow one
 // another through Y [n][n], and a lane group takes one column; waves 4 to 7
 // take the partner columns of waves 0 to 3 and read the same kernel values.
-// 128x128x1024: 313 us on eight-lane transforms -> 237, of which about 140 are
-// vector issue; the rest is the latency that two waves per SIMD leave open between
-// barriers that all eight meet (planes and H^ held in L2: 222, so not memory).
+// 128x128x1024: 313 us on eight-lane transforms -> 241 (events).  Vector issue takes
+// 64 % of the SIMDs' busy cycles; the rest is the latency that two waves per SIMD
+// leave open between barriers that all eight meet.  Planes and H^ held in L2 took
+// 222 of what was then 237 us, so memory is the smaller part, although the plane
+// that is read a second time, and H^ passing through L2 between, make 2.04 times the
+// bytes that the pass cannot do without.  14 registers are spilled (52 bytes).
 template <int LOGN, bool ADJ, int PAD, bool PACKED>
 __device__ __forceinline__ void plane_conv_wide_body(float2* __restrict__ P, const float2* Hp,
                                                      float2* Y, float2* tw2, float2 tv, int tid) {
