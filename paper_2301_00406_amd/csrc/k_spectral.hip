@@ -983,8 +983,9 @@ __device__ __forceinline__ void quad_columns(float2* const (&Yc)[NC], const floa
 }
 
 // n <= 64: a block per kt plane, Y [n][2 n] with the even ky first.  Bound by
-// vector issue (64x64x512: 82 % of the SIMDs' busy cycles, 47 % of each wave's; 0.58
-// of the instructions of the eight-lane form, whose cross-lane stages took half).
+// vector issue (64x64x512: 77 to 82 % of the SIMDs' busy cycles, 44 to 47 % of each
+// wave's; 0.58 of the instructions of the eight-lane form, whose cross-lane stages
+// took half).
 // SPLIT = 1 (n = 64): 4 n threads; a lane group takes both ky halves of its row
 // and the columns ky and -ky.  SPLIT = 2 (n <= 32): 8 n threads; the second half
 // of the waves takes the odd ky and the columns -ky, and the two halves of a
@@ -1111,12 +1112,13 @@ k_plane_conv_quad(float2* __restrict__ spec, const float2* __restrict__ hq,
 // n = 128: the padded plane does not fit LDS, so the ky halves follow one
 // another through Y [n][n], and a lane group takes one column; waves 4 to 7
 // take the partner columns of waves 0 to 3 and read the same kernel values.
-// 128x128x1024: 313 us on eight-lane transforms -> 241 (events).  Vector issue takes
-// 64 % of the SIMDs' busy cycles; the rest is the latency that two waves per SIMD
-// leave open between barriers that all eight meet.  Planes and H^ held in L2 took
-// 222 of what was then 237 us, so memory is the smaller part, although the plane
-// that is read a second time, and H^ passing through L2 between, make 2.04 times the
-// bytes that the pass cannot do without.  14 registers are spilled (52 bytes).
+// 128x128x1024: 313 us on eight-lane transforms -> 243 by events, 245 in the trace of
+// a reconstruction.  Vector issue takes 65 % of the SIMDs' busy cycles; the rest is
+// the latency that two waves per SIMD leave open between barriers that all eight
+// meet.  Planes and H^ held in L2 took 222 instead of 237 us (operator alone), so
+// memory is the smaller part, although the plane that is read a second time, and H^
+// passing through L2 between, make 2.05 times the bytes that the pass cannot do
+// without.  14 registers are spilled (52 bytes per lane).
 template <int LOGN, bool ADJ, int PAD, bool PACKED>
 __device__ __forceinline__ void plane_conv_wide_body(float2* __restrict__ P, const float2* Hp,
                                                      float2* Y, float2* tw2, float2 tv, int tid) {
