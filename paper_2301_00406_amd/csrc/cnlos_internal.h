@@ -474,7 +474,7 @@ struct NcGeo {
   int n, m;
   double wall, range, cdt, ix, iy;
   int literal;
-  int plain;      // set by the launchers: distances beyond the fast path's range
+  int plain;      // set by launch_nc_forward: distances beyond the fast path's range
 };
 hipError_t launch_nc_forward(const NcGeo& g, const float* u, float* tau, hipStream_t st);
 hipError_t launch_nc_transpose(const NcGeo& g, const float* tau, float* u, hipStream_t st);

@@ -358,22 +358,18 @@ k_nc_transpose(NcGeo g, const float* __restrict__ tau, float* __restrict__ u) {
   double acc = 0.0;
   for (int i = 0; i < n; ++i) {
     const double x2 = lx[i];
-    int ja = 0, jb = n;
-    if (!g.plain) {
-      // the detectors of the row within reach, and one on either side
-      const double rem = lat - x2, w = sqrt(fmax(rem, 0.0)) * per;
-      ja = max(0, (int)fmax(jv - w, 0.0) - 1);
-      jb = rem < 0.0 ? 0 : min(n, (int)fmin(jv + w, (double)n) + 2);
-    }
-    ja = __builtin_amdgcn_readfirstlane(ja);
-    jb = __builtin_amdgcn_readfirstlane(jb);
+    // the detectors of the row within reach, and one on either side
+    const double rem = lat - x2, w = sqrt(fmax(rem, 0.0)) * per;
+    const int ja = __builtin_amdgcn_readfirstlane(max(0, (int)fmax(jv - w, 0.0) - 1));
+    const int jb = __builtin_amdgcn_readfirstlane(
+        rem < 0.0 ? 0 : min(n, (int)fmin(jv + w, (double)n) + 2));
     // four detectors at a time: their loads are unconditional (bin clamped into
     // the column, value masked) and issue together, and one branch serves the
     // rare bins of all four
     for (int j0 = ja; j0 < jb; j0 += 4) {
       NcFast f[4];
       const float* td[4];       // in scalar registers
-      bool near = g.plain != 0;
+      bool near = false;
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         td[q] = tau + (size_t)__builtin_amdgcn_readfirstlane((i * n + min(j0 + q, n - 1)) * m);
@@ -386,7 +382,6 @@ k_nc_transpose(NcGeo g, const float* __restrict__ tau, float* __restrict__ u) {
         for (int q = 0; q < 4; ++q) {
           const NcPath r = nc_path(g, nc_lateral(g, i), nc_lateral(g, min(j0 + q, n - 1)), xv, yv, zp, di);
           f[q].bin = j0 + q < n ? r.bin : m;
-          if (g.plain) f[q].r2 = f[q].bin < m ? r.w : 0.0;
         }
       }
       float t[4];
@@ -401,11 +396,41 @@ k_nc_transpose(NcGeo g, const float* __restrict__ tau, float* __restrict__ u) {
       }
     }
   }
-  if (LIT && !g.plain) {
+  if (LIT) {
     const double ri = 1.0 / di;
     acc *= ri * ri;
   }
   if (k0 + lane < m && (int)blockIdx.x * kNcTWaves + wv < items) u[(size_t)col * m + k] = (float)acc;
+}
+
+// The same sum with a voxel per thread and the plain path: for geometries beyond
+// the fast path's range, and for large grids with few bins (launch_nc_transpose).
+__global__ void __launch_bounds__(256)
+k_nc_transpose_plain(NcGeo g, const float* __restrict__ tau, float* __restrict__ u) {
+  __shared__ double xs[kNcMaxGridDev];
+  const int m = g.m, n = g.n;
+  for (int i = threadIdx.x; i < n; i += 256) xs[i] = nc_lateral(g, i);
+  __syncthreads();
+  const size_t V = (size_t)n * n * m;
+  const size_t vox = (size_t)blockIdx.x * 256 + threadIdx.x;
+  if (vox >= V) return;
+  const int col = (int)(vox / m), k = (int)(vox - (size_t)col * m);
+  const double xv = xs[col / n], yv = xs[col % n], z = nc_depth(g, k);
+  const double di = nc_illum_dist(g, xv, yv, z);
+  double acc = 0.0;
+  for (int i = 0; i < n; ++i) {
+    const double xd = xs[i];
+    // loads are unconditional (bin clamped into the column, term masked), so
+    // the unrolled iterations' loads issue together
+#pragma unroll 4
+    for (int j = 0; j < n; ++j) {
+      const NcPath r = nc_path(g, xd, xs[j], xv, yv, z, di);
+      const int b = r.bin < m ? r.bin : m - 1;
+      const float t = tau[(size_t)(i * n + j) * m + b];
+      acc += r.bin < m ? r.w * (double)t : 0.0;
+    }
+  }
+  u[vox] = (float)acc;
 }
 
 }  // namespace
@@ -462,9 +487,19 @@ hipError_t launch_nc_forward(const NcGeo& g0, const float* u, float* tau, hipStr
   return hipGetLastError();
 }
 
-hipError_t launch_nc_transpose(const NcGeo& g0, const float* tau, float* u, hipStream_t st) {
-  NcGeo g = g0;
-  g.plain = nc_in_range(g) ? 0 : 1;
+hipError_t launch_nc_transpose(const NcGeo& g, const float* tau, float* u, hipStream_t st) {
+  // A wave of k_nc_transpose takes one column whatever its depths, a thread of the
+  // plain form one voxel at 2.8 times the cost of a path.  With up to 64 x 64
+  // columns the waves of the first fit the chip at once, so idle lanes cost nothing
+  // (64x64x16: 931 us and 932 with the plain form); beyond, with few depths, the
+  // plain form is faster: 100x100x8 3.29 against 4.89 ms, 128x128x8 5.25 / 12.3,
+  // 128x128x20 11.3 / 12.3, 256x256x1 14.5 / 186; 128x128x24 13.3 / 12.3.
+  if (!nc_in_range(g) || (g.n > 64 && g.m < 24)) {
+    const size_t V = (size_t)g.n * g.n * g.m;
+    hipLaunchKernelGGL(k_nc_transpose_plain, dim3((unsigned)((V + 255) / 256)), dim3(256), 0, st, g,
+                       tau, u);
+    return hipGetLastError();
+  }
   const int items = g.n * g.n * ((g.m + 63) / 64);
   const dim3 grid((items + kNcTWaves - 1) / kNcTWaves), block(64 * kNcTWaves);
   const size_t lds = (size_t)kNcTWaves * (2 * g.n + 1) * sizeof(double);

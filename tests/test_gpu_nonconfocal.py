@@ -219,3 +219,48 @@ def test_paths_beyond_the_window(n, m, wall, dt, illum, literal):
     assert np.array_equal(tau != 0.0, ref != 0.0) and np.array_equal(ut != 0.0, ref_t != 0.0)
     assert rel_l2(tau, ref) <= TOL and max_rel(tau, ref) <= TOL
     assert rel_l2(ut, ref_t) <= TOL and max_rel(ut, ref_t) <= TOL
+
+
+# the transpose's choice between a wave per column and a voxel per thread: the
+# smallest grid and the most bins of the second form, and one step beyond either
+@pytest.mark.parametrize("n,m", [(65, 1), (65, 23), (65, 24), (64, 23)])
+def test_transpose_of_few_bins(n, m):
+    torch = need_gpu()
+    say(f"nonconfocal transpose n={n} m={m}")
+    wall, dt, illum = 0.9, 20.0 * 512 / m, (0.21, -0.13)
+    g, og = _geoms(n, m, wall, dt, illum, True)
+    t = f32(scenes.random_signed((n, n, m), 53 + m))
+    ut = to_host(C.nc_apply_T(g, to_dev(torch, t)))
+    x, z = og.lateral(), og.depth()
+    D = (x[:, None] - x[None, :]) ** 2                  # [detector][voxel] along one axis
+    for p, q in [(0, 0), (n - 1, n // 2), (n // 3, n - 1)]:
+        di = np.sqrt((x[p] - illum[0]) ** 2 + (x[q] - illum[1]) ** 2 + z ** 2)
+        dd = np.sqrt(D[:, p][:, None, None] + D[:, q][None, :, None] + z ** 2)
+        b = np.floor((di + dd) / og.bin_length()).astype(np.int64)
+        v = np.take_along_axis(t, np.minimum(b, m - 1), axis=2)
+        ref = np.where(b < m, v / (di * di * dd * dd), 0.0).sum(axis=(0, 1))
+        assert rel_l2(ut[p, q], ref) <= TOL and max_rel(ut[p, q], ref) <= TOL
+
+
+def test_transpose_time_follows_the_bins():
+    """A column of one bin does not cost a large grid what one of 64 bins does."""
+    torch = need_gpu()
+
+    def ms(n, m):
+        g, _ = _geoms(n, m, 0.9, 20.0 * 512 / m, (0.21, -0.13), True)
+        x = torch.rand((n, n, m), device="cuda")
+        out = torch.empty_like(x)
+        C.nc_apply_T(g, x, out)
+        best = float("inf")
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            C.nc_apply_T(g, x, out)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b))
+        return best
+
+    one, many = ms(128, 1), ms(128, 64)
+    say(f"transpose at 128x128: {one:.2f} ms with 1 bin, {many:.2f} with 64")
+    assert one <= 0.6 * many
