@@ -1214,7 +1214,7 @@ cnlos_status build_tables(cnlos_problem* p, const cnlos_config* cfg, const uint8
   std::vector<float4> srows, scols;
   if (const char* why = resample_descriptors(m, srows, scols)) return fail(CNLOS_EINVAL, why);
   std::vector<float2> fa, fb;
-  column_twiddles(p->logm, fa, fb);
+  column_twiddles(p->logm, tw_t, fa, fb);
   if ((int)std::max(fa.size(), fb.size()) * 2 > column_tw_floats(m))
     return fail(CNLOS_EINVAL, "twiddle table larger than its bound");
   std::vector<float> wk(m), r3(m), sig_xy(n), sig_t(m / 2 + 1);

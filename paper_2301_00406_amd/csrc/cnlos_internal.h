@@ -326,7 +326,8 @@ __host__ __device__ constexpr RzIndex rz_index(int bits) {
   return {k0, k2, lg ? k0 + 1 : 0, lg ? k2 : 0, lg};
 }
 const char* resample_descriptors(int m, std::vector<float4>& rows, std::vector<float4>& cols);
-void column_twiddles(int logm, std::vector<float2>& fa, std::vector<float2>& fb);
+void column_twiddles(int logm, const std::vector<float2>& tw, std::vector<float2>& fa,
+                     std::vector<float2>& fb);
 
 // XCD-aware block order.  Workgroups are dealt round-robin over the 8 XCDs,
 // each with its own L2; logical block xcd_block(b, nb) places nb / 8

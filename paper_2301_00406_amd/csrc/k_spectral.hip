@@ -2026,21 +2026,25 @@ k_build_hq(float2* __restrict__ hq, int m, const int* __restrict__ dq,
 // blocks of the t passes (their partial sums are indexed by block)
 int conv_blocks(int logn, int logm) { return (1 << (2 * logn)) / t_columns(logm); }
 // tables of the passes' lane twiddles (fft_column.h) for a time axis of 2^logm
-// bins: the convolution's transform, then the solve's
-void column_twiddles(int logm, std::vector<float2>& fa, std::vector<float2>& fb) {
-  const double PI = 3.14159265358979323846;
+// bins: the convolution's transform, then the solve's.  tw: exp(-pi i j / m), j < m,
+// which holds every root that they need (a sine and a cosine per entry instead took
+// 36 us of a problem's creation at 1024 bins).
+void column_twiddles(int logm, const std::vector<float2>& tw, std::vector<float2>& fa,
+                     std::vector<float2>& fb) {
+  const int m = 1 << logm;
   fa.clear();
   fb.clear();
-  auto w = [&](double num, double den) {
-    return make_float2((float)cos(-2.0 * PI * num / den), (float)sin(-2.0 * PI * num / den));
+  auto w = [&](int num, int den) {                 // exp(-2 pi i num / den), den divides 2 m
+    const int j = (num * (2 * m / den)) & (2 * m - 1);
+    return j < m ? tw[j] : make_float2(-tw[j - m].x, -tw[j - m].y);
   };
   for (int logf : {logm, logm - 1}) {
     if (logf < 8 || logf > 10) continue;
     const int F = 1 << logf, E = F / 64, low = E == 8 ? 7 : E == 4 ? 15 : 3;
     for (int k = 1; k < E; ++k)
       for (int l = 0; l < 64; ++l) {
-        fa.push_back(w((double)l * k, F));
-        fb.push_back(w((double)(l & low) * k, 64));
+        fa.push_back(w(l * k, F));
+        fb.push_back(w((l & low) * k, 64));
       }
     if (E == 4)
       for (int j = 0; j < 16; ++j) fb.push_back(w(j, 16));
