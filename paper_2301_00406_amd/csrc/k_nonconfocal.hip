@@ -318,7 +318,7 @@ k_nc_forward(NcGeo g, const float* __restrict__ u, float* __restrict__ tau) {
 // detector rows and columns are tables in LDS that the wave reads as
 // broadcasts, and a path's squared distance is two additions.  Detectors beyond
 // the reach of the wave's shallowest depth are left out, row by row.  Bound by FP64
-// issue: 45x45x300 2.61 -> 1.09 ms, 24x24x224 with a 1.5 m wall 0.14 -> 0.075.
+// issue: 45x45x300 2.60 -> 1.05 ms, 24x24x224 with a 1.5 m wall 0.14 -> 0.075.
 constexpr int kNcTWaves = 4;
 template <bool LIT>
 __global__ void __launch_bounds__(64 * kNcTWaves)
